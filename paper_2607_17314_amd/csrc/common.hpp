@@ -94,6 +94,11 @@ struct GemmArgs {
 
 xtc_status gemm_f64(const GemmArgs& g, hipStream_t st);
 
+// Up to GEMM_LIST independent products of the same M, N, K, k-contiguity, presence of s and
+// lower_only in one launch, so that products too small to fill the chip fill it together.
+constexpr int GEMM_LIST = 9;
+xtc_status gemm_f64_list(const GemmArgs* g, int count, hipStream_t st);
+
 // Rejects quadrature weights that are negative, NaN or infinite (XTC_ERR_INVALID_ARG):
 // one small kernel over grid->w with an integer flag in the first bytes of the caller's
 // workspace, then a synchronisation of the stream to read the flag. Called before any

@@ -109,6 +109,13 @@ __global__ __launch_bounds__(256) void k_form_V(const double* __restrict__ panel
                    H[2 * bp + g] * panel[(2 * rows_pad + nu) * bp + g];
 }
 
+// d += x[0..n) + x[n..2n), one after the other
+__global__ __launch_bounds__(256) void k_add2(double* __restrict__ d, const double* __restrict__ x,
+                                              long n) {
+  const long i = (long)blockIdx.x * 256 + threadIdx.x;
+  if (i < n) d[i] = (d[i] + x[i]) + x[n + i];
+}
+
 __global__ void k_mul(const double* __restrict__ a, const double* __restrict__ b, long n,
                       double* __restrict__ out) {
   long i = (long)blockIdx.x * 256 + threadIdx.x;
@@ -121,6 +128,7 @@ struct ConLayout {
   void* gsplit; size_t gsplit_bytes; BHTable* bh;
   void* gsplit2;   // second operand scratch: the u1/u3 products on the auxiliary stream
   double* pv64;    // FP64 path, BH form: the pair values of one ket launch
+  double* d4x;     // FP64 path: the y and z parts of a super-block's D4
   // xi~ per bra super-block: the orbitals at the pivots, xi~ of the block, solve scratch
   double* phimu; double* xigb; double* fitP; double* fitR;
   long bp; long rows_pad; int nsb; int nch;
@@ -167,6 +175,9 @@ static ConLayout layout_con(Arena& ar, int64_t n_g, int n_mu, uint32_t channels,
   C.bh = ar.take<BHTable>(1);
   C.pv64 = (bh && precision == XTC_FP64) ? ar.take<double>(bh_f64_pv_bytes(C.bp) / sizeof(double))
                                          : nullptr;
+  C.d4x = (dual && precision == XTC_FP64 && (channels & XTC_D4))
+              ? ar.take<double>(2 * (size_t)n_mu * n_mu)
+              : nullptr;
   C.phimu = C.xigb = C.fitP = C.fitR = nullptr;
   if (xig_blocks && (channels & XTC_U1)) {
     C.phimu = ar.take<double>(4 * (size_t)n_orb * n_mu);
@@ -355,8 +366,12 @@ static xtc_status contract_impl(const xtc_grid* grid, const xtc_correlator* corr
       XTC_HIP(hipEventRecord(ev_fork, st));
       XTC_HIP(hipStreamWaitEvent(st2, ev_fork, 0));
     }
+    // FP64 path: the products of the super-block are collected and run in one launch (each
+    // has (n_mu / 128)^2 tiles, 144 at n_mu = 1500: alone they leave most of the chip idle)
+    GemmArgs batch[GEMM_LIST];
+    int n_batch = 0;
     auto nt = [&](const double* A, long a_sm, const double* s, const double* B, double* out,
-                  double bet, hipStream_t ss, void* gs, const float* A32 = nullptr) {
+                  double bet, hipStream_t ss, void* gs, const float* A32 = nullptr) -> xtc_status {
       GemmArgs g{};
       g.M = n_mu; g.N = n_mu; g.K = bn;
       g.A = A; g.a_sm = a_sm; g.a_sk = 1;
@@ -365,8 +380,9 @@ static xtc_status contract_impl(const xtc_grid* grid, const xtc_correlator* corr
       g.B = B; g.b_sk = 1; g.b_sn = C.bp;
       g.C = out; g.c_sm = n_mu; g.c_sn = 1;
       g.beta = bet;
-      return precision == XTC_SPLIT_F16 ? gemm_split_nt(g, gs, C.gsplit_bytes, ss)
-                                        : gemm_f64(g, ss);
+      if (precision == XTC_SPLIT_F16) return gemm_split_nt(g, gs, C.gsplit_bytes, ss);
+      batch[n_batch++] = g;
+      return XTC_OK;
     };
     // (w xi) T^T for a panel channel, xi in FP64 or FP32
     auto nt_xi = [&](const double* B, double* out, double bet, hipStream_t ss, void* gs) {
@@ -398,17 +414,42 @@ static xtc_status contract_impl(const xtc_grid* grid, const xtc_correlator* corr
                        (const double*)C.panel, C.rows_pad, C.bp, need_h ? 1 : 0, C.wt, C.H, C.e3x,
                        C.e4x, C.e3, C.e4, (channels & XTC_FIELD) ? field : nullptr);
     XTC_CHECK_LAUNCH();
-    if (channels & XTC_D4)
-      for (int c = 0; c < 3; ++c) {
-        const double* Pc = C.panel + (long)c * C.rows_pad * C.bp;
-        XTC_TRY(nt(Pc, C.bp, C.wt, Pc, D4, (sb == 0 && c == 0) ? 0.0 : 1.0, st, C.gsplit));
-      }
+    const double bet4 = sb == 0 ? 0.0 : 1.0;
+    auto d4 = [&](int c, double* out, double bet) {
+      const double* Pc = C.panel + (long)c * C.rows_pad * C.bp;
+      return nt(Pc, C.bp, C.wt, Pc, out, bet, st, C.gsplit);
+    };
     if (channels & XTC_D1) {
       hipLaunchKernelGGL(k_form_V, dim3(cdiv((long)n_mu * bn, 256)), dim3(256), 0, st,
                          (const double*)C.panel, C.rows_pad, C.bp, n_mu, bn, (const double*)C.H,
                          C.V);
       XTC_CHECK_LAUNCH();
-      XTC_TRY(nt_xi(C.V, D1, beta, st, C.gsplit));
+    }
+    if (precision == XTC_FP64) {
+      const long nn = (long)n_mu * n_mu;
+      const bool d4_parts = (channels & XTC_D4) && C.d4x;
+      if (channels & XTC_D1) XTC_TRY(nt_xi(C.V, D1, beta, st, nullptr));
+      if (d4_parts) {
+        XTC_TRY(d4(0, D4, bet4));
+        XTC_TRY(d4(1, C.d4x, 0.0));
+        XTC_TRY(d4(2, C.d4x + nn, 0.0));
+      }
+      if (n_batch > 0) XTC_TRY(gemm_f64_list(batch, n_batch, st));
+      if (d4_parts) {
+        hipLaunchKernelGGL(k_add2, dim3(cdiv(nn, 256)), dim3(256), 0, st, D4,
+                           (const double*)C.d4x, nn);
+        XTC_CHECK_LAUNCH();
+      } else if (channels & XTC_D4) {   // no scratch for the parts: one after the other
+        for (int c = 0; c < 3; ++c) {
+          n_batch = 0;
+          XTC_TRY(d4(c, D4, c == 0 ? bet4 : 1.0));
+          XTC_TRY(gemm_f64(batch[0], st));
+        }
+      }
+    } else {
+      if (channels & XTC_D4)
+        for (int c = 0; c < 3; ++c) XTC_TRY(d4(c, D4, c == 0 ? bet4 : 1.0));
+      if (channels & XTC_D1) XTC_TRY(nt_xi(C.V, D1, beta, st, C.gsplit));
     }
     XTC_TRY(reduce_sum_f64(C.e3x, bn, C.sums + 4 * sb, C.red, st));
     XTC_TRY(reduce_sum_f64(C.e4x, bn, C.sums + 4 * sb + 1, C.red, st));

@@ -2,146 +2,407 @@
 // deterministic reductions. Used by the orbital GEMM, the fit (Gram, RHS,
 // Cholesky updates, blocked triangular solves) and stage 2 of the contraction.
 //
-// Tile 64 x 64 x 16, 256 threads = 4 wave64s arranged 2 x 2; each wave owns a
-// 32 x 32 sub-tile = 2 x 2 MFMA blocks of 16 x 16. Operands are staged through
-// LDS k-major (row stride 65 doubles, so k-contiguous staging writes hit
-// distinct banks); the next k-tile is prefetched into registers while the
-// current one is multiplied.
+// Tiles of 128 x 128, 64 x 128 or 64 x 64 by 16, 256 threads = 4 wave64s arranged 2 x 2.
+// Bound: the FP64 matrix rate (77.6 TFLOP/s measured in registers), and with it the issue
+// slots: the matrix instructions share their pipe with the vector ALU and are issued in
+// program order, so every address instruction between two of them counts. Operands go
+// global -> registers -> LDS with one k-tile (64 x 64: two) in registers, one being
+// multiplied and one being stored, one barrier per k-tile; fragments are double-buffered
+// in registers so no MFMA waits for LDS. 8192 x 8192 x 4096: 55.5 -> 69.3 TFLOP/s (MFMA
+// busy 92% of the cycles), 22,500 x 1,500 x 4,500: 51 -> 60, 64 x 58,200 x 1,408: 36.7 -> 46.
+// Each output sums its products in the same order in every shape.
 //
 // MFMA 16x16x4 f64 register layout (per lane l of the wave):
 //   A operand: A[l % 16][l / 16]      B operand: B[l / 16][l % 16]
 //   D (4 doubles): D[(l / 16) + 4 r][l % 16], r = 0..3  (measured on gfx950)
+#include <type_traits>
 #include "common.hpp"
 
 namespace xtc {
 
 typedef double d4 __attribute__((ext_vector_type(4)));
 
-constexpr int GT = 64;    // tile M and N
 constexpr int GK = 16;    // tile K
-constexpr int LDS_LD = GT + 1;
 
-template <bool A_KCONT, bool B_KCONT>
-__global__ __launch_bounds__(256) void k_gemm_f64(GemmArgs g) {
-  __shared__ double As[GK][LDS_LD];
-  __shared__ double Bs[GK][LDS_LD];
+// Element (k, row) of a BT-row operand tile in LDS. Counted in 8-byte slots modulo the 32
+// of one LDS pass, row 0 of k sits at 16 (k & 1) + 2 (k >> 1): the 16 rows by 2 k's that
+// half a wave reads as MFMA fragments, the 16 k's by 2 rows that it stores of a
+// k-contiguous operand and the 32 rows of one k that it stores of the others each fall
+// into 32 different slots.
+template <int BT>
+__host__ __device__ __forceinline__ constexpr int lds_at(int k, int row) {
+  return k * BT + (k >> 1) * 34 + (k & 1) * 16 + row;
+}
+template <int BT>
+constexpr int LDS_TILE = GK * BT + (GK / 2) * 34;
+
+// Pins a value to scalar registers, or a vector one as the base that constant offsets are
+// added to: without them the compiler folds the scalar part of an address into a vector
+// multiply-add per load, and a vector add per LDS store.
+typedef const __attribute__((address_space(1))) char* GlobalBytes;
+typedef const __attribute__((address_space(1))) double* GlobalF64;
+__device__ __forceinline__ void keep_scalar(GlobalBytes& p) { asm("" : "+s"(p)); }
+template <class T>
+__device__ __forceinline__ void keep_vector(T& x) { asm("" : "+v"(x)); }
+
+// One operand's share of a thread: BT / 16 elements of each BT x 16 tile, in registers
+// between the load and the store to LDS.
+//   KCONT:  element i is (row tid / 16 + 16 i, k tid % 16);
+//   else:   element i is (row tid % BT, k tid / BT + (256 / BT) i), k uniform over a wave.
+// Rows past the operand's end read its last row (their products are not stored); k's past
+// K read K - 1 and are zeroed before the store (mask), tiles past the last one read it again.
+// The matrix instructions share their pipe with the vector ALU, so the addresses are kept
+// off it: a scalar pointer that moves with k plus per-thread byte offsets that stay, 32-bit
+// (WIDE: 64-bit, for row strides of 2^22 elements and more).
+template <int BT, bool KCONT, bool WIDE, int DEPTH>
+struct TileLoader {
+  static constexpr int N = BT / 16;
+  static constexpr int G = 256 / BT;
+  using Off = typename std::conditional<WIDE, unsigned long, unsigned>::type;
+  GlobalBytes base;   // the tile's first row, k = 0
+  GlobalBytes next;   // the first element of the next whole tile for this thread's wave
+  long sk, K, step;
+  Off off[KCONT ? N : 1];
+  int k_first;
+  double v[DEPTH][N];
+
+  __device__ __forceinline__ TileLoader(const double* X, long s_row, long s_k, long r0, long rows,
+                                        long K_, int tid)
+      : base((GlobalBytes)(X + r0 * s_row)), sk(8 * s_k), K(K_) {
+    if constexpr (KCONT) {
+      k_first = tid & 15;
+#pragma unroll
+      for (int i = 0; i < N; ++i) {
+        long r = (tid >> 4) + 16 * i;
+        if (r > rows - 1 - r0) r = rows - 1 - r0;
+        off[i] = (Off)(8 * (r * s_row + k_first));
+      }
+      next = base;
+      step = 0;
+    } else {
+      long r = tid % BT;
+      if (r > rows - 1 - r0) r = rows - 1 - r0;
+      off[0] = (Off)(8 * r * s_row);
+      k_first = __builtin_amdgcn_readfirstlane(tid / BT);
+      next = base + k_first * sk;
+      step = G * sk;
+    }
+  }
+  __device__ __forceinline__ int k_of(int i) const {   // k of element i within the tile
+    return KCONT ? k_first : k_first + G * i;
+  }
+  // The next tile, all of whose k's are below K; tiles come in order.
+  __device__ __forceinline__ void load_whole(int q) {
+    GlobalBytes p = next;
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      keep_scalar(p);
+      Off o = off[KCONT ? i : 0];
+      if constexpr (!WIDE) keep_vector(o);
+      v[q][i] = *(GlobalF64)(p + o);
+      if constexpr (!KCONT) p += step;
+    }
+    next += GK * sk;
+  }
+  // The tile from k0: k's past K read K - 1.
+  __device__ __forceinline__ void load_any(int q, long k0) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      const long k = k0 + k_of(i) < K ? k0 + k_of(i) : K - 1;
+      v[q][i] = *(GlobalF64)(base + (KCONT ? off[KCONT ? i : 0] + 8 * (k - k_first) : k * sk + off[0]));
+    }
+  }
+  __device__ __forceinline__ void mask(int q, long k0) {
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+      if (k0 + k_of(i) >= K) v[q][i] = 0.0;
+  }
+  __device__ __forceinline__ void store(int q, double* lds, int at) const {   // at: store_at + buffer
+    keep_vector(at);
+#pragma unroll
+    for (int i = 0; i < N; ++i) lds[at + (KCONT ? 16 * i : lds_at<BT>(G * i, 0))] = v[q][i];
+  }
+  __device__ __forceinline__ int store_at(int tid) const {
+    return lds_at<BT>(k_first, KCONT ? tid >> 4 : tid % BT);
+  }
+};
+
+// M tiles of one group: the 64 tiles in flight on an XCD then cover 8 row and 8 column panels
+constexpr long GROUP_M = 8;
+
+// The products of one launch (blockIdx.y), all of the same shape.
+struct GemmList {
+  GemmArgs g[GEMM_LIST];
+};
+
+// BM x BN output tile per workgroup, four waves 2 x 2.
+template <int BM, int BN, bool A_KCONT, bool B_KCONT, bool SCALE, bool WIDE>
+__global__ __launch_bounds__(256, 2) void k_gemm_f64(GemmList list) {
+  const GemmArgs& g = list.g[blockIdx.y];
+  constexpr int MI = BM / 32, NI = BN / 32;   // 16 x 16 blocks per wave
+  constexpr int SA = LDS_TILE<BM>, SB = LDS_TILE<BN>;
+  __shared__ __align__(16) double As[2 * SA];
+  __shared__ __align__(16) double Bs[2 * SB];
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = tid >> 6;
   const int wm = wave >> 1, wn = wave & 1;
-  // Tile order: the M tile runs fastest, so the workgroups that read the same
-  // column panel of B run at the same time, and consecutive workgroup ids (which
-  // the hardware deals to the 8 XCDs in turn) are spread so that each XCD takes a
-  // contiguous run of tiles and shares those panels in its own L2.
-  const long n_mt = (g.M + GT - 1) / GT, n_tiles = n_mt * ((g.N + GT - 1) / GT);
+  // Tile order: groups of GROUP_M M tiles, the M tile fastest within one, so the
+  // workgroups that read the same panels of A and B run at the same time, and
+  // consecutive workgroup ids (which the hardware deals to the 8 XCDs in turn) are
+  // spread so that each XCD takes a contiguous run of tiles and shares those panels in
+  // its own L2.
+  const long n_mt = (g.M + BM - 1) / BM, n_nt = (g.N + BN - 1) / BN, n_tiles = n_mt * n_nt;
   const long per_xcd = (n_tiles + 7) / 8;
   const long t = (long)(blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
   if (t >= n_tiles) return;   // the whole workgroup, before any barrier
-  const long m0 = (t % n_mt) * GT;
-  const long n0 = (t / n_mt) * GT;
-  if (g.lower_only && m0 + GT - 1 < n0) return;
+  const long in_group = GROUP_M * n_nt, group = t / in_group, tg = t % in_group;
+  const long gm = n_mt - group * GROUP_M < GROUP_M ? n_mt - group * GROUP_M : GROUP_M;
+  const long m0 = (group * GROUP_M + tg % gm) * BM;
+  const long n0 = (tg / gm) * BN;
+  if (g.lower_only && m0 + BM - 1 < n0) return;
 
-  double ra[4], rb[4];
-  auto load = [&](long k0) {
+  constexpr int DEPTH = BM == 64 && BN == 64 ? 2 : 1;
+  TileLoader<BM, A_KCONT, WIDE, DEPTH> la(g.A, g.a_sm, g.a_sk, m0, g.M, g.K, tid);
+  TileLoader<BN, B_KCONT, WIDE, DEPTH> lb(g.B, g.b_sn, g.b_sk, n0, g.N, g.K, tid);
+  const int wa = la.store_at(tid), wb = lb.store_at(tid);
+  constexpr int NS = A_KCONT ? 1 : BM / 16;
+  double sv[DEPTH][NS];
+  auto load = [&](auto whole, int q, long k0) {
+    if constexpr (whole.value) {
+      la.load_whole(q);
+      lb.load_whole(q);
+    } else {
+      la.load_any(q, k0);
+      lb.load_any(q, k0);
+    }
+    if constexpr (SCALE) {
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      int e = tid + 256 * j;
-      int mm, kk;
-      if (A_KCONT) { kk = e % GK; mm = e / GK; } else { mm = e % GT; kk = e / GT; }
-      long m = m0 + mm, k = k0 + kk;
-      double v = 0.0;
-      if (m < g.M && k < g.K) {
-        v = g.A[m * g.a_sm + k * g.a_sk];
-        if (g.s) v *= g.s[k];
+      for (int i = 0; i < NS; ++i) {
+        const long k = k0 + la.k_of(i);
+        sv[q][i] = g.s[whole.value || k < g.K ? k : g.K - 1];
       }
-      ra[j] = v;
-      int nn;
-      if (B_KCONT) { kk = e % GK; nn = e / GK; } else { nn = e % GT; kk = e / GT; }
-      long n = n0 + nn;
-      k = k0 + kk;
-      rb[j] = (n < g.N && k < g.K) ? g.B[k * g.b_sk + n * g.b_sn] : 0.0;
     }
   };
-  auto stash = [&]() {
+  auto store = [&](auto whole, int q, int buf, long k0) {   // the loaded tile, whose first k is k0
+    if constexpr (SCALE) {
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      int e = tid + 256 * j;
-      int mm, kk;
-      if (A_KCONT) { kk = e % GK; mm = e / GK; } else { mm = e % GT; kk = e / GT; }
-      As[kk][mm] = ra[j];
-      int nn;
-      if (B_KCONT) { kk = e % GK; nn = e / GK; } else { nn = e % GT; kk = e / GT; }
-      Bs[kk][nn] = rb[j];
+      for (int i = 0; i < BM / 16; ++i) la.v[q][i] *= sv[q][A_KCONT ? 0 : i];
     }
+    if (!whole.value && k0 + GK > g.K) {
+      la.mask(q, k0);
+      lb.mask(q, k0);
+    }
+    la.store(q, As, wa + buf * SA);
+    lb.store(q, Bs, wb + buf * SB);
   };
 
-  d4 acc[2][2];
+  d4 acc[MI][NI];
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int i = 0; i < MI; ++i)
 #pragma unroll
-    for (int j = 0; j < 2; ++j) acc[i][j] = (d4){0.0, 0.0, 0.0, 0.0};
+    for (int j = 0; j < NI; ++j) acc[i][j] = (d4){0.0, 0.0, 0.0, 0.0};
 
   const int li = lane & 15, lk = lane >> 4;
-  load(0);
-  for (long k0 = 0; k0 < g.K; k0 += GK) {
-    __syncthreads();
-    stash();
-    __syncthreads();
-    if (k0 + GK < g.K) load(k0 + GK);
+  const int ra = lds_at<BM>(lk, (BM / 2) * wm + li);
+  const int rb = lds_at<BN>(lk, (BN / 2) * wn + li);
+  // Fragments of MFMA step s (k = 4 s .. 4 s + 3) of a buffer, double-buffered in registers:
+  // step s + 1's are read while step s multiplies, step 0 of the next tile's during step 3.
+  double fa[2][MI], fb[2][NI];
+  auto read = [&](int buf, int s) {
+    int pa = ra + buf * SA, pb = rb + buf * SB;
+    keep_vector(pa);
+    keep_vector(pb);
 #pragma unroll
-    for (int s = 0; s < GK / 4; ++s) {
-      double a0 = As[4 * s + lk][32 * wm + li];
-      double a1 = As[4 * s + lk][32 * wm + 16 + li];
-      double b0 = Bs[4 * s + lk][32 * wn + li];
-      double b1 = Bs[4 * s + lk][32 * wn + 16 + li];
-      acc[0][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, b0, acc[0][0], 0, 0, 0);
-      acc[0][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, b1, acc[0][1], 0, 0, 0);
-      acc[1][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, b0, acc[1][0], 0, 0, 0);
-      acc[1][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, b1, acc[1][1], 0, 0, 0);
+    for (int i = 0; i < MI; ++i) fa[s & 1][i] = As[pa + lds_at<BM>(4 * s, 0) + 16 * i];
+#pragma unroll
+    for (int j = 0; j < NI; ++j) fb[s & 1][j] = Bs[pb + lds_at<BN>(4 * s, 0) + 16 * j];
+  };
+  auto multiply = [&](int s) {
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+      for (int j = 0; j < NI; ++j)
+        acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(fa[s & 1][i], fb[s & 1][j], acc[i][j], 0, 0, 0);
+  };
+  // Two k-tiles in flight beside the one being multiplied: during step 0 the next tile goes
+  // from registers to the other LDS buffer and the one after it is requested, so the loads
+  // have a whole tile's time to arrive and the stores are long done at the barrier before
+  // step 3.
+  constexpr std::true_type whole{};
+  constexpr std::false_type any{};
+  int buf = 0;
+  auto reads_first = [&]() {   // the step's fragment reads go ahead of its MFMAs
+    __builtin_amdgcn_sched_group_barrier(0x100, MI + NI, 0);
+    __builtin_amdgcn_sched_group_barrier(0x008, MI * NI, 0);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  // multiplies tile k0 - GK, stores tile k0 (from registers q), requests tile k0 + DEPTH GK
+  auto tile = [&](auto w, int q, long k0) {
+    read(buf, 1);
+    store(w, q, buf ^ 1, k0);
+    load(w, q, k0 + DEPTH * GK);
+    multiply(0);
+    // step 0: the fragment reads, then one LDS store and one load beside each MFMA
+    __builtin_amdgcn_sched_group_barrier(0x100, MI + NI, 0);
+#pragma unroll
+    for (int i = 0; i < MI * NI; ++i) {
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+      __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);
+      __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
     }
-  }
+    __builtin_amdgcn_sched_barrier(0);
+    read(buf, 2);
+    multiply(1);
+    reads_first();
+    read(buf, 3);
+    multiply(2);
+    reads_first();
+    __builtin_amdgcn_s_waitcnt(0xc07f);
+    __syncthreads();
+    buf ^= 1;
+    read(buf, 0);
+    multiply(3);
+    reads_first();
+  };
+  long k0 = GK;
+  auto first = [&](auto w) {
+    load(w, 0, 0);
+    store(w, 0, 0, 0);
 #pragma unroll
-  for (int bi = 0; bi < 2; ++bi)
+    for (int q = 0; q < DEPTH; ++q) load(w, q, (1 + q) * GK);
+  };
+  if ((DEPTH + 1) * GK <= g.K) first(whole);
+  else first(any);
+  __builtin_amdgcn_s_waitcnt(0xc07f);   // LDS stores done before the barrier
+  __syncthreads();
+  read(0, 0);
+  for (; k0 + 2 * DEPTH * GK <= g.K; k0 += DEPTH * GK)
 #pragma unroll
-    for (int bj = 0; bj < 2; ++bj)
+    for (int q = 0; q < DEPTH; ++q) tile(whole, q, k0 + q * GK);
+  for (; k0 < g.K; k0 += DEPTH * GK)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        long m = m0 + 32 * wm + 16 * bi + lk + 4 * r;
-        long n = n0 + 32 * wn + 16 * bj + li;
-        if (m >= g.M || n >= g.N) continue;
-        double v = g.alpha * acc[bi][bj][r];
-        if (g.sn) v *= g.sn[n];
-        if (g.beta != 0.0) {
-          const double* D = g.D ? g.D : g.C;
-          v += g.beta * D[m * g.c_sm + n * g.c_sn];
+    for (int q = 0; q < DEPTH; ++q)
+      if (k0 + q * GK < g.K) tile(any, q, k0 + q * GK);
+  read(buf, 1);
+  multiply(0);
+  read(buf, 2);
+  multiply(1);
+  read(buf, 3);
+  multiply(2);
+  multiply(3);
+  // Epilogue, 16 rows at a time: the C (or D) and E values that the rows need are all
+  // requested before the first is used. Whole tiles skip the bounds checks; offsets are a
+  // per-thread part plus a scalar one.
+  const long mt = m0 + (BM / 2) * wm, nt = n0 + (BN / 2) * wn;   // the wave's first row, column
+  const double* D = g.D ? g.D : g.C;
+  const long c0 = (mt + lk) * g.c_sm + (nt + li) * g.c_sn;
+  const long e0 = (mt + lk) * g.e_sm + (nt + li) * g.e_sn;
+  auto emit = [&](auto full) {
+#pragma unroll
+    for (int bi = 0; bi < MI; ++bi) {
+      double d[NI][4], e[NI][4];
+      auto in = [&](int bj, int r) {
+        return full.value || (mt + lk + 16 * bi + 4 * r < g.M && nt + li + 16 * bj < g.N);
+      };
+      if (g.beta != 0.0)
+#pragma unroll
+        for (int bj = 0; bj < NI; ++bj)
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+            if (in(bj, r)) d[bj][r] = D[c0 + ((16 * bi + 4 * r) * g.c_sm + 16 * bj * g.c_sn)];
+      if (g.epi == EPI_MUL_E)
+#pragma unroll
+        for (int bj = 0; bj < NI; ++bj)
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+            if (in(bj, r)) e[bj][r] = g.E[e0 + ((16 * bi + 4 * r) * g.e_sm + 16 * bj * g.e_sn)];
+#pragma unroll
+      for (int bj = 0; bj < NI; ++bj) {
+        double sn = 1.0;
+        if (g.sn && in(bj, 0)) sn = g.sn[nt + li + 16 * bj];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          double v = g.alpha * acc[bi][bj][r];
+          if (g.sn) v *= sn;
+          if (g.beta != 0.0) v += g.beta * d[bj][r];
+          if (g.epi == EPI_MUL_E) v *= e[bj][r];
+          else if (g.epi == EPI_SQUARE) v *= v;
+          if (in(bj, r)) g.C[c0 + ((16 * bi + 4 * r) * g.c_sm + 16 * bj * g.c_sn)] = v;
         }
-        if (g.epi == EPI_MUL_E) v *= g.E[m * g.e_sm + n * g.e_sn];
-        else if (g.epi == EPI_SQUARE) v *= v;
-        g.C[m * g.c_sm + n * g.c_sn] = v;
       }
+    }
+  };
+  if (m0 + BM <= g.M && n0 + BN <= g.N) emit(whole);
+  else emit(any);
 }
 
-xtc_status gemm_f64(const GemmArgs& g, hipStream_t st) {
-  XTC_REQUIRE(g.A32 == nullptr, "gemm_f64: FP32 operands are for the split GEMM only");
-  if (g.M <= 0 || g.N <= 0) return XTC_OK;
-  if (g.K <= 0) {
-    set_error("gemm_f64: K must be positive");
-    return XTC_ERR_INVALID_ARG;
-  }
-  const long n_tiles = ((g.M + GT - 1) / GT) * ((g.N + GT - 1) / GT);
+template <int BM, int BN, bool WIDE = false>
+static xtc_status launch_gemm(const GemmList& list, int n, hipStream_t st) {
+  const GemmArgs& g = list.g[0];
+  const long n_tiles = ((g.M + BM - 1) / BM) * ((g.N + BN - 1) / BN);
   const long n_wg = 8 * ((n_tiles + 7) / 8);
   if (n_wg > 0x7fffffffL) {
     set_error("gemm_f64: too many tiles for one launch");
     return XTC_ERR_INVALID_ARG;
   }
-  const dim3 grid((unsigned)n_wg);
-  bool ak = (g.a_sk == 1), bk = (g.b_sk == 1);
-  if (ak && bk) hipLaunchKernelGGL((k_gemm_f64<true, true>), grid, dim3(256), 0, st, g);
-  else if (ak && !bk) hipLaunchKernelGGL((k_gemm_f64<true, false>), grid, dim3(256), 0, st, g);
-  else if (!ak && bk) hipLaunchKernelGGL((k_gemm_f64<false, true>), grid, dim3(256), 0, st, g);
-  else hipLaunchKernelGGL((k_gemm_f64<false, false>), grid, dim3(256), 0, st, g);
+  const dim3 grid((unsigned)n_wg, (unsigned)n);
+  const bool ak = (g.a_sk == 1), bk = (g.b_sk == 1);
+  auto go = [&](auto A, auto B) {
+    if (g.s)
+      hipLaunchKernelGGL((k_gemm_f64<BM, BN, A.value, B.value, true, WIDE>), grid, dim3(256), 0, st, list);
+    else
+      hipLaunchKernelGGL((k_gemm_f64<BM, BN, A.value, B.value, false, WIDE>), grid, dim3(256), 0, st, list);
+  };
+  if (ak && bk) go(std::true_type{}, std::true_type{});
+  else if (ak) go(std::true_type{}, std::false_type{});
+  else if (bk) go(std::false_type{}, std::true_type{});
+  else go(std::false_type{}, std::false_type{});
   XTC_CHECK_LAUNCH();
   return XTC_OK;
+}
+
+xtc_status gemm_f64(const GemmArgs& g, hipStream_t st) { return gemm_f64_list(&g, 1, st); }
+
+xtc_status gemm_f64_list(const GemmArgs* gs, int count, hipStream_t st) {
+  const GemmArgs& g = gs[0];
+  XTC_REQUIRE(count >= 1 && count <= GEMM_LIST, "gemm_f64: bad number of products");
+  // 32-bit offsets within a tile of at most 128 rows
+  constexpr long FAR = 1L << 22;
+  bool wide = false;
+  GemmList list;
+  for (int i = 0; i < count; ++i) {
+    const GemmArgs& h = gs[i];
+    XTC_REQUIRE(h.A32 == nullptr, "gemm_f64: FP32 operands are for the split GEMM only");
+    XTC_REQUIRE(h.M == g.M && h.N == g.N && h.K == g.K && (h.a_sk == 1) == (g.a_sk == 1) &&
+                    (h.b_sk == 1) == (g.b_sk == 1) && !h.s == !g.s && h.lower_only == g.lower_only,
+                "gemm_f64: the products of one launch must have one shape");
+    wide = wide || h.a_sm >= FAR || h.b_sn >= FAR;
+    list.g[i] = h;
+  }
+  if (g.M <= 0 || g.N <= 0) return XTC_OK;
+  if (g.K <= 0) {
+    set_error("gemm_f64: K must be positive");
+    return XTC_ERR_INVALID_ARG;
+  }
+  // Time of a shape, in units of one element at the full rate of one of the 256 CUs: whole
+  // rounds of tiles per CU (one workgroup alone keeps a CU's matrix pipes about as busy as
+  // several) over the rate that the shape reaches at 8192 x 8192 x 4096.
+  auto tiles = [&](long bm, long bn) {
+    const long mt = (g.M + bm - 1) / bm, nt = (g.N + bn - 1) / bn;
+    return count * (g.lower_only ? (mt * nt + (mt > nt ? mt : nt)) / 2 : mt * nt);
+  };
+  auto cost = [&](long bm, long bn, double rate) {
+    return (double)((tiles(bm, bn) + 255) / 256 * bm * bn) / rate;
+  };
+  if (wide) return launch_gemm<64, 64, true>(list, count, st);
+  // up to two tiles per CU the smallest shape ends first: its tiles are in flight together
+  // (60 x 17,200 x 60: 11.5 us against 13.4 with 64 x 128 tiles)
+  if (tiles(64, 64) <= 512) return launch_gemm<64, 64>(list, count, st);
+  const double c1 = cost(128, 128, 69.0), c2 = cost(64, 128, 66.0), c3 = cost(64, 64, 64.0);
+  if (c1 <= c2 && c1 <= c3) return launch_gemm<128, 128>(list, count, st);
+  if (c2 <= c3) return launch_gemm<64, 128>(list, count, st);
+  return launch_gemm<64, 64>(list, count, st);
 }
 
 // ---------------------------------------------------------------------------

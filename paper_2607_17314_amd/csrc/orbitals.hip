@@ -1,7 +1,7 @@
 // Orbital and orbital-gradient values on the grid (Alg. 2, grid step).
 // One thread per grid point evaluates every AO value and Cartesian gradient of
 // a grid chunk into an SoA buffer ao4[4][n_ao][chunk]; the MO values follow as
-// four FP64 MFMA GEMMs phi4[c] = C_mo^T ao4[c]; rho_gamma is a per-point sum
+// four FP64 MFMA GEMMs phi4[c] = C_mo^T ao4[c] in one launch; rho_gamma is a per-point sum
 // over the occupied orbitals.
 #include "common.hpp"
 #include "plans.hpp"
@@ -169,15 +169,17 @@ extern "C" xtc_status xtc_eval_orbitals(const xtc_basis* basis, const xtc_grid* 
     hipLaunchKernelGGL(k_eval_ao, dim3(cdiv(cn, 256)), dim3(256), 0, st, b, grid->xyz, n_g, g0,
                        L.chunk, L.ao4);
     XTC_CHECK_LAUNCH();
+    GemmArgs gs[4];
     for (int c = 0; c < 4; ++c) {
-      GemmArgs g{};
+      GemmArgs& g = gs[c];
+      g = GemmArgs{};
       g.M = n_orb; g.N = cn; g.K = n_ao;
       g.A = C_mo; g.a_sm = 1; g.a_sk = n_orb;
       g.B = L.ao4 + (long)c * n_ao * L.chunk; g.b_sk = L.chunk; g.b_sn = 1;
       g.s = nullptr;
       g.C = phi4 + (long)c * n_orb * n_g + g0; g.c_sm = n_g; g.c_sn = 1;
-      XTC_TRY(gemm_f64(g, st));
     }
+    XTC_TRY(gemm_f64_list(gs, 4, st));
   }
   if (rho) {
     hipLaunchKernelGGL(k_density, dim3(cdiv(n_g, 256)), dim3(256), 0, st, phi4, n_g, n_occ, rho);
