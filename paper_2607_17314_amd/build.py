@@ -36,10 +36,11 @@ FLAGS = [
 # bitwise the same results), and shuttles the adjoint kernels' values between the
 # two register files (fewer registers and spills in the VGPR form: EE adjoint 8%,
 # BH adjoint 22% faster). The option is not applied globally: it crashes the
-# compiler on the FP64 stage-1 kernels.
+# compiler on the BH form's FP64 stage-1 kernel (stage1_f64.hip).
 FILE_FLAGS = {
     "gemm_f64.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
     "grad.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
+    "stage1_products.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
 }
 
 

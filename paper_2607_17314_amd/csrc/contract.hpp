@@ -40,6 +40,10 @@ struct Stage1Args {
 };
 
 xtc_status stage1_f64(const Stage1Args& a, const EECoef& cf, hipStream_t st);
+// its products (stage1_products.hip): the EE form whole, or one ket launch of the BH form's
+// pair values in a.pv64 (kets [kbeg, kbeg + 16 nsteps))
+xtc_status stage1_ee_f64(const Stage1Args& a, const EECoef& cf, hipStream_t st);
+xtc_status stage1_pv_f64(const Stage1Args& a, long nsteps, long kbeg, hipStream_t st);
 xtc_status stage1_split_f16(const Stage1Args& a, const EECoef& cf, void* scratch,
                             size_t scratch_bytes, hipStream_t st);
 size_t split_scratch_bytes(long n_g, int n_mu);

@@ -1,6 +1,6 @@
 // The two density rows of the stage-1 panel in FP64 for the split path (the split
 // pair kernel leaves them out): rows n_mu (rho_gamma) and n_mu + 1 (the ISDF density).
-#include "contract.hpp"
+#include "ee_pair.hpp"
 
 namespace xtc {
 
@@ -9,45 +9,8 @@ namespace xtc {
 // rhot (H_{g,c}, which as a sum over N_mu split-precision rows would cancel).
 // Each thread takes two bra points and one ket segment (the ket values are
 // wave-uniform, so they come through the scalar cache); the segments' partial
-// sums are added in a fixed order by k_rho_row_sum. 1/sqrt and 1/(1 + d r) start
-// from the hardware estimates and take two Newton steps (about one ulp; FP64
-// division and square root would each expand to a longer correctly-rounded
-// sequence), and the polynomials have a compile-time length NQ (coefficients
-// past the true degree are zero).
+// sums are added in a fixed order by k_rho_row_sum.
 constexpr int RHO_SEG = 32;
-
-template <int NQ>
-__device__ __forceinline__ double horner_fixed(const double (&q)[NQ], double x) {
-  double r = q[NQ - 1];
-#pragma unroll
-  for (int j = NQ - 2; j >= 0; --j) r = fma(r, x, q[j]);
-  return r;
-}
-
-// r = |d| and 1/r (0 and 0 at r = 0) from r2 = |d|^2
-__device__ __forceinline__ void sqrt_rsqrt(double r2, double& r, double& rinv) {
-  double y = __builtin_amdgcn_rsq(r2);            // ~1/sqrt(r2)
-  double g = r2 * y, h = 0.5 * y;                  // g ~ sqrt(r2), h ~ 1/(2 sqrt(r2))
-#pragma unroll
-  for (int it = 0; it < 2; ++it) {
-    const double e = fma(-h, g, 0.5);
-    g = fma(g, e, g);
-    h = fma(h, e, h);
-  }
-  const bool zero = !(r2 > 0.0);
-  r = zero ? 0.0 : g;
-  rinv = zero ? 0.0 : 2.0 * h;
-}
-
-__device__ __forceinline__ double recip(double x) {   // x >= 1
-  double y = __builtin_amdgcn_rcp(x);
-#pragma unroll
-  for (int it = 0; it < 2; ++it) {
-    const double e = fma(-x, y, 1.0);
-    y = fma(y, e, y);
-  }
-  return y;
-}
 
 template <int NQ, bool C1>
 __global__ __launch_bounds__(256) void k_rho_row(const double* __restrict__ xyz,
