@@ -13,18 +13,17 @@
 // d lap u/dc_k = lap_k, with f_k, u'_k, lap_k the kernels of the unit coefficient e_k.
 // The kernel tiles are regenerated from coordinates; the D cotangents add one
 // recomputation of the forward panel per bra super-block.
+#include <type_traits>
 #include "bh.hpp"
-#include "contract.hpp"
+#include "ee_pair.hpp"
+#include "mfma_f64.hpp"
 #include "plans.hpp"
 #include "timing.hpp"
 
 namespace xtc {
 
-typedef double d4 __attribute__((ext_vector_type(4)));
-
 constexpr long GSUPER = 16384;
-constexpr int GT = 64;        // bra x ket tile
-constexpr int GK = 16;        // rows per LDS stage
+constexpr int RK = GK;        // rows per LDS stage
 constexpr int KSEG = 8;       // ket segments (grid y)
 
 struct GradBasis {
@@ -87,168 +86,327 @@ __device__ __forceinline__ void pair_grad(const EECoef& cf, const GradBasis& gb,
   if (gb.want_d) dth[gb.n] += dd;
 }
 
-// M_c(b, k) = sum_row Pbar[c][row][b] A[row][k] over the workgroup's 64 x 64 pair tile,
-// rows in steps of GK through LDS. With PF the next step's tiles are loaded into registers
-// while the current step's MFMAs run (the pair kernels run one wave per SIMD, so nothing
-// else hides the load latency); kernels without the registers for it load in place.
-template <int NCH, bool PF>
-__device__ __forceinline__ void m_tiles(const double* __restrict__ Pb, long rows_pad, long bp,
-                                        int n_rows, const double* __restrict__ xi,
-                                        const double* __restrict__ rho,
-                                        const double* __restrict__ rhot,
-                                        const double* __restrict__ w, long n_g, int n_mu,
-                                        long bt0, long bn, long kc, long k_hi,
-                                        double (*Gs)[GK][GT + 1], double (*As)[GT + 1],
-                                        d4 (&acc)[NCH][2][2]) {
-  constexpr int NG = NCH * GK * GT / 256, NA = GK * GT / 256;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave >> 1, wn = wave & 1;
-  const int li = lane & 15, lk = lane >> 4;
-  double pg[NG], pa[NA];
-  auto fetch = [&](int r0) {
-    // Pbar tile: NCH x GK rows x 64 bra (bra contiguous in memory)
+// The M tiles on the matrix cores, in the pipeline of the FP64 GEMM (gemm_f64.hip): a
+// workgroup (4 waves 2 x 2) holds NCH channels of BT bra x KT ket points, wave (wm, wn) bra
+// points 16 wm .. + 15 and kets (KT / 2) wn .. + KT / 2 - 1, 16 x 16 per MFMA block:
+// acc[c][j][r] = sum_mu Pbar[c][mu][b] xi[mu][k] at b = 16 wm + lane / 16 + 4 r,
+// k = (KT / 2) wn + 16 j + lane % 16. The two density rows and the ket weight are applied
+// per pair (pair_cotangents). 16-row steps go global -> registers -> LDS, one step in
+// registers, one being stored, one being multiplied.
+constexpr int BT = 32;   // bra points per workgroup
+
+template <int NCH, int KT>
+struct MTile {
+  static constexpr int NJ = KT / 32;
+  static constexpr int NG = NCH * BT * RK / 256, NA = KT * RK / 256;
+  static constexpr int SG = LDS_TILE<NCH * BT>, SA = LDS_TILE<KT>;
+  static constexpr int LDS = 2 * (SG + SA);   // doubles
+  static constexpr int GCOLS = NCH * BT;
+  static constexpr bool ONE_COL = 256 % GCOLS == 0;   // all of a thread's elements in one column
+  double* sm;
+  GlobalF64 pb[ONE_COL ? 1 : NG];   // Pbar elements of this thread: (column e % GCOLS, row e / GCOLS)
+  long bp, rows;
+  const double* xi;
+  long n_g;
+  int tid, krow;                    // krow: first ket-operand row of this thread's wave
+  double vg[NG], va[NA];
+
+  __device__ __forceinline__ MTile(double* sm_, const double* Pb, long rows_pad, long bp_, int n_mu,
+                                   long bt0, long bn, const double* xi_, long n_g_, int tid_)
+      : sm(sm_), bp(bp_), rows(n_mu), xi(xi_), n_g(n_g_), tid(tid_),
+        krow(__builtin_amdgcn_readfirstlane(tid_ / KT)) {
+#pragma unroll
+    for (int q = 0; q < (ONE_COL ? 1 : NG); ++q) {
+      const int e = tid + 256 * q, col = e % GCOLS;
+      long b = bt0 + col % BT;
+      if (b > bn - 1) b = bn - 1;   // its products are not used
+      pb[q] = (GlobalF64)(Pb + ((long)(col / BT) * rows_pad + e / GCOLS) * bp + b);
+    }
+  }
+  // Rows r0 .. r0 + 15 of the Pbar columns and of kets kc .. (kets past the grid read the last
+  // one, their products are not used; rows past n_mu read the last row and are zeroed).
+  __device__ __forceinline__ void load(bool whole, long r0, long kc) {
 #pragma unroll
     for (int q = 0; q < NG; ++q) {
-      const int e = tid + 256 * q;
-      const int c = e / (GK * GT), rr = (e / GT) % GK, bb = e % GT;
-      const long row = r0 + rr, b = bt0 + bb;
-      pg[q] = (row < n_rows && b < bn) ? Pb[((long)c * rows_pad + row) * bp + b] : 0.0;
+      const int row = (tid + 256 * q) / GCOLS;
+      long r = r0 + (ONE_COL ? 256 / GCOLS * q : 0);
+      if (!whole && r0 + row > rows - 1) r = rows - 1 - (ONE_COL ? tid / GCOLS : row);
+      vg[q] = pb[ONE_COL ? 0 : q][r * bp];
     }
-    // A tile: GK rows x 64 ket
+    long k = kc + tid % KT;
+    if (k > n_g - 1) k = n_g - 1;
+    const unsigned off = 8u * (unsigned)(k - kc);
 #pragma unroll
     for (int q = 0; q < NA; ++q) {
-      const int e = tid + 256 * q;
-      const int rr = e / GT, kk = e % GT;
-      const long row = r0 + rr, g = kc + kk;
-      double v = 0.0;
-      if (row < n_rows && g < k_hi)
-        v = w[g] * (row < n_mu ? xi[row * n_g + g] : (row == n_mu ? rho[g] : rhot[g]));
-      pa[q] = v;
+      long r = r0 + krow + 256 / KT * q;
+      if (!whole && r > rows - 1) r = rows - 1;
+      GlobalBytes p = (GlobalBytes)(xi + r * n_g + kc);
+      keep_scalar(p);
+      unsigned o = off;
+      keep_vector(o);
+      va[q] = *(GlobalF64)(p + o);
     }
-  };
+  }
+  __device__ __forceinline__ void store(bool whole, int buf, long r0) {
 #pragma unroll
-  for (int c = 0; c < NCH; ++c)
+    for (int q = 0; q < NG; ++q) {
+      const int e = tid + 256 * q, row = e / GCOLS;
+      if (!whole && r0 + row >= rows) vg[q] = 0.0;
+      int at = buf * SG + (ONE_COL ? lds_at<GCOLS>(tid / GCOLS, tid % GCOLS) : lds_at<GCOLS>(row, e % GCOLS));
+      if (ONE_COL) keep_vector(at);
+      sm[at + (ONE_COL ? lds_at<GCOLS>(256 / GCOLS * q, 0) : 0)] = vg[q];
+    }
+    int at = 2 * SG + buf * SA + lds_at<KT>(krow, tid % KT);
+    keep_vector(at);
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int q = 0; q < NA; ++q) {
+      if (!whole && r0 + krow + 256 / KT * q >= rows) va[q] = 0.0;
+      sm[at + lds_at<KT>(256 / KT * q, 0)] = va[q];
+    }
+  }
+  // The products of ket tile kc. Ends with a barrier, so LDS may be written again.
+  __device__ __forceinline__ void products(long kc, d4 (&acc)[NCH][NJ]) {
+    const int lane = tid & 63, wave = tid >> 6, wm = wave >> 1, wn = wave & 1;
+    const int li = lane & 15, lk = lane >> 4;
+    const int rg = lds_at<GCOLS>(lk, 16 * wm + li);
+    const int ra = 2 * SG + lds_at<KT>(lk, (KT / 2) * wn + li);
 #pragma unroll
-      for (int j = 0; j < 2; ++j) acc[c][i][j] = (d4){0.0, 0.0, 0.0, 0.0};
-  if (PF) fetch(0);
-  for (int r0 = 0; r0 < n_rows; r0 += GK) {
+    for (int c = 0; c < NCH; ++c)
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) acc[c][j] = (d4){0.0, 0.0, 0.0, 0.0};
+    double fg[2][NCH], fa[2][NJ];
+    auto read = [&](int buf, int st) {
+      int og = rg + buf * SG, oa = ra + buf * SA;
+      keep_vector(og);
+      keep_vector(oa);
+#pragma unroll
+      for (int c = 0; c < NCH; ++c) fg[st & 1][c] = sm[og + lds_at<GCOLS>(4 * st, 0) + BT * c];
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) fa[st & 1][j] = sm[oa + lds_at<KT>(4 * st, 0) + 16 * j];
+    };
+    auto multiply = [&](int st) {
+#pragma unroll
+      for (int c = 0; c < NCH; ++c)
+#pragma unroll
+        for (int j = 0; j < NJ; ++j)
+          acc[c][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(fg[st & 1][c], fa[st & 1][j], acc[c][j], 0, 0, 0);
+    };
+    int buf = 0;
+    auto step = [&](auto w, long r0) {   // multiplies r0 - RK, stores r0, requests r0 + RK
+      read(buf, 1);
+      store(w.value, buf ^ 1, r0);
+      load(w.value, r0 + RK, kc);
+      multiply(0);
+      __builtin_amdgcn_sched_group_barrier(0x100, NCH + NJ, 0);
+#pragma unroll
+      for (int i = 0; i < NCH * NJ; ++i) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int h = 1; h < 4; ++h) {
+        if (h < 3) {
+          read(buf, h + 1);
+        } else {
+          __builtin_amdgcn_s_waitcnt(0xc07f);
+          __syncthreads();
+          buf ^= 1;
+          read(buf, 0);
+        }
+        multiply(h);
+        __builtin_amdgcn_sched_group_barrier(0x100, NCH + NJ, 0);
+        __builtin_amdgcn_sched_group_barrier(0x008, NCH * NJ, 0);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    };
+    load(false, 0, kc);
+    store(false, 0, 0);
+    load(false, RK, kc);
+    __builtin_amdgcn_s_waitcnt(0xc07f);   // LDS stores done before the barrier
     __syncthreads();
-    if (PF) {
+    read(0, 0);
+    long r0 = RK;
+    for (; r0 + 2 * RK <= rows; r0 += RK) step(std::true_type{}, r0);
+    for (; r0 < rows; r0 += RK) step(std::false_type{}, r0);
 #pragma unroll
-      for (int q = 0; q < NG; ++q) {
-        const int e = tid + 256 * q;
-        Gs[e / (GK * GT)][(e / GT) % GK][e % GT] = pg[q];
-      }
-#pragma unroll
-      for (int q = 0; q < NA; ++q) {
-        const int e = tid + 256 * q;
-        As[e / GT][e % GT] = pa[q];
-      }
-    } else {
-      for (int e = tid; e < NCH * GK * GT; e += 256) {
-        const int c = e / (GK * GT), rr = (e / GT) % GK, bb = e % GT;
-        const long row = r0 + rr, b = bt0 + bb;
-        Gs[c][rr][bb] = (row < n_rows && b < bn) ? Pb[((long)c * rows_pad + row) * bp + b] : 0.0;
-      }
-      for (int e = tid; e < GK * GT; e += 256) {
-        const int rr = e / GT, kk = e % GT;
-        const long row = r0 + rr, g = kc + kk;
-        double v = 0.0;
-        if (row < n_rows && g < k_hi)
-          v = w[g] * (row < n_mu ? xi[row * n_g + g] : (row == n_mu ? rho[g] : rhot[g]));
-        As[rr][kk] = v;
-      }
+    for (int h = 0; h < 4; ++h) {
+      if (h < 3) read(buf, h + 1);
+      multiply(h);
     }
     __syncthreads();
-    if (PF && r0 + GK < n_rows) fetch(r0 + GK);
-#pragma unroll
-    for (int s = 0; s < GK / 4; ++s) {
-      const double b0v = As[4 * s + lk][32 * wn + li];
-      const double b1v = As[4 * s + lk][32 * wn + 16 + li];
-#pragma unroll
-      for (int c = 0; c < NCH; ++c) {
-        const double a0 = Gs[c][4 * s + lk][32 * wm + li];
-        const double a1 = Gs[c][4 * s + lk][32 * wm + 16 + li];
-        acc[c][0][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, b0v, acc[c][0][0], 0, 0, 0);
-        acc[c][0][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, b1v, acc[c][0][1], 0, 0, 0);
-        acc[c][1][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, b0v, acc[c][1][0], 0, 0, 0);
-        acc[c][1][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, b1v, acc[c][1][1], 0, 0, 0);
-      }
-    }
+  }
+};
+
+// The bra side of a workgroup's pairs in LDS: coordinates and the two density rows of Pbar.
+template <int NCH>
+struct BraRows {
+  double xyz[3][BT];
+  double rho[2][NCH][BT];
+};
+
+template <int NCH>
+__device__ __forceinline__ void fill_bra_rows(BraRows<NCH>& B, const double* xyz, long n_g, long b0,
+                                              long bt0, long bn, const double* Pb, long rows_pad,
+                                              long bp, int n_mu, int tid) {
+  for (int e = tid; e < 3 * BT; e += 256) {
+    long b = bt0 + e % BT;
+    if (b > bn - 1) b = bn - 1;
+    B.xyz[e / BT][e % BT] = xyz[(e / BT) * n_g + b0 + b];
+  }
+  for (int e = tid; e < 2 * NCH * BT; e += 256) {
+    const int row = e / (NCH * BT), c = e / BT % NCH;
+    long b = bt0 + e % BT;
+    if (b > bn - 1) b = bn - 1;
+    B.rho[row][c][e % BT] = Pb[((long)c * rows_pad + n_mu + row) * bp + b];
   }
 }
 
-template <int NCH>
-__global__ __launch_bounds__(256) void k_grad_pairs(
-    const double* __restrict__ Pb, long rows_pad, long bp, int n_rows,
-    const double* __restrict__ xi, const double* __restrict__ rho, const double* __restrict__ rhot,
-    const double* __restrict__ w, const double* __restrict__ xyz, long n_g, int n_mu, long b0,
-    long bn, EECoef cf, GradBasis gb, double* __restrict__ partials) {
-  __shared__ double Gs[NCH][GK][GT + 1];   // Pbar rows x bra
-  __shared__ double As[GK][GT + 1];        // A rows x ket
-  __shared__ double bxyz[3][GT];
-  __shared__ double kxyz[3][GT];
-  __shared__ double red[4][MAXQ + 1];
+// m[c] = w_k (M products + the density rows) of one pair
+template <int NCH, int NJ>
+__device__ __forceinline__ void pair_cotangents(const d4 (&acc)[NCH][NJ], int j, int r,
+                                                const BraRows<NCH>& B, int bi, double wk,
+                                                double rho_k, double rhot_k, double* m) {
+#pragma unroll
+  for (int c = 0; c < NCH; ++c)
+    m[c] = wk * fma(B.rho[1][c][bi], rhot_k, fma(B.rho[0][c][bi], rho_k, acc[c][j][r]));
+}
+
+// Sums over pairs from which the derivatives follow: with sf = M_vec . Delta, s3 = 2 u' M_sq,
+//   S_j = sum sf d^2 t^3 rbar^j,  U_j = sum s3 d t^2 rbar^j,  S1 = sum sf d t^2 / r,
+//   dL/dc_k = o (S_{o-2} + U_{o-1}) for o >= 2 and S1 + U_0 for o = 1.
+// NQ >= the highest power. WANT_D: also dL/dd, from d/dd [d^2 t^3 e^m] = d t^3 e^m (2 - 3e + m t)
+// and d/dd [d t^2 e^m] = t^2 e^m (1 - 2e + m t) summed over the terms with their coefficients.
+template <int NQ, bool WANT_D>
+struct PowerSums {
+  double S[NQ], U[NQ], S1, dd;
+  __device__ __forceinline__ void clear() {
+#pragma unroll
+    for (int j = 0; j < NQ; ++j) S[j] = U[j] = 0.0;
+    S1 = dd = 0.0;
+  }
+  __device__ __forceinline__ void add(const EECoef& cf, double dx, double dy, double dz,
+                                      const double* m) {
+    const double d = cf.d;
+    double r, rinv;
+    sqrt_rsqrt(fma(dx, dx, fma(dy, dy, dz * dz)), r, rinv);
+    const double t = recip(fma(d, r, 1.0));
+    const double e = d * r * t, dt2 = d * t * t;
+    double p1 = 0.0;
+#pragma unroll
+    for (int j = NQ - 1; j >= 0; --j) p1 = fma(p1, e, cf.q1[j]);   // zeros past the degree
+    const double sf = fma(m[0], dx, fma(m[1], dy, m[2] * dz));
+    const double s3 = 2.0 * dt2 * p1 * m[3];
+    double a = sf * dt2 * d * t, b = s3 * dt2;
+    S1 = fma(sf * dt2, rinv, S1);
+    if (WANT_D) {
+      double p1e = 0.0, p2 = 0.0, p2e = 0.0;   // e Q1', Q2, e Q2'
+#pragma unroll
+      for (int j = NQ - 1; j >= 0; --j) {
+        p1e = fma(p1e, e, j * cf.q1[j]);
+        p2 = fma(p2, e, cf.q2[j]);
+        p2e = fma(p2e, e, j * cf.q2[j]);
+      }
+      const double t2 = t * t;
+      const double fd = d * t2 * t * fma(2.0 - 3.0 * e, p2, t * p2e) +
+                        (r > 0.0 ? cf.c1 * t2 * (rinv - 2.0 * d * t) : 0.0);
+      const double upd = t2 * fma(1.0 - 2.0 * e, p1, t * p1e);
+      dd += fma(sf, fd, s3 * upd);
+    }
+#pragma unroll
+    for (int j = 0; j < NQ; ++j) {
+      S[j] += a;
+      U[j] += b;
+      a *= e;
+      b *= e;
+    }
+  }
+};
+
+// One workgroup: bra tile blockIdx.x x the ket tiles of segment blockIdx.y. Bound: the FP64
+// matrix rate; the pairs' derivative terms (~90 vector instructions each) come once per
+// n_mu / 4 matrix instructions of a block. NQ > 0: the power sums above (four channels);
+// NQ = 0: pair_grad, whose parameter loop is dynamic (the Laplacian). Each ket tile's sums are
+// added over the wave and into LDS, so the tile loop carries no accumulators. One of four
+// bra shards of an eight-atom chain (46,560 points, N_mu 1,200): 222 -> 88 ms (23 -> 59
+// TFLOP/s of products; the 64 x 64 tiles ran one wave per SIMD with two barriers a step).
+template <int NCH, int NQ, bool WANT_D>
+__global__ __launch_bounds__(256, 2) void k_grad_pairs(
+    const double* __restrict__ Pb, long rows_pad, long bp, const double* __restrict__ xi,
+    const double* __restrict__ rho, const double* __restrict__ rhot, const double* __restrict__ w,
+    const double* __restrict__ xyz, long n_g, int n_mu, long b0, long bn, EECoef cf, GradBasis gb,
+    double* __restrict__ partials) {
+  constexpr int KT = NCH == 4 ? 128 : 64;
+  using Tile = MTile<NCH, KT>;
+  constexpr int NS = NQ > 0 ? 2 * NQ + 1 + WANT_D : MAXQ + 1;
+  __shared__ __align__(16) double sm[Tile::LDS];
+  __shared__ BraRows<NCH> B;
+  __shared__ double red[4][NS];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave >> 1, wn = wave & 1;
-  const int li = lane & 15, lk = lane >> 4;
-  const long bt0 = (long)blockIdx.x * GT;               // bra tile origin within the block
-  const long per = ((n_g + KSEG - 1) / KSEG + GT - 1) / GT * GT;
+  const int wm = wave >> 1, wn = wave & 1, li = lane & 15, lk = lane >> 4;
+  const long bt0 = (long)blockIdx.x * BT;
+  const long per = ((n_g + KSEG - 1) / KSEG + KT - 1) / KT * KT;
   const long k_lo = (long)blockIdx.y * per;
   const long k_hi = k_lo + per < n_g ? k_lo + per : n_g;
-  if (tid < GT) {
-    long b = b0 + bt0 + tid;
-    if (b > b0 + bn - 1) b = b0 + bn - 1;
-    bxyz[0][tid] = xyz[b];
-    bxyz[1][tid] = xyz[n_g + b];
-    bxyz[2][tid] = xyz[2 * n_g + b];
-  }
-  double dth[MAXQ + 1];
-  for (int k = 0; k <= MAXQ; ++k) dth[k] = 0.0;
-
-  for (long kc = k_lo; kc < k_hi; kc += GT) {
-    __syncthreads();
-    if (tid < GT) {
-      long g = kc + tid;
-      if (g > n_g - 1) g = n_g - 1;
-      kxyz[0][tid] = xyz[g];
-      kxyz[1][tid] = xyz[n_g + g];
-      kxyz[2][tid] = xyz[2 * n_g + g];
+  fill_bra_rows(B, xyz, n_g, b0, bt0, bn, Pb, rows_pad, bp, n_mu, tid);
+  for (int e = tid; e < 4 * NS; e += 256) red[e / NS][e % NS] = 0.0;
+  Tile T(sm, Pb, rows_pad, bp, n_mu, bt0, bn, xi, n_g, tid);
+  for (long kc = k_lo; kc < k_hi; kc += KT) {
+    d4 acc[NCH][Tile::NJ];
+    T.products(kc, acc);
+    double dth[MAXQ + 1];
+    PowerSums<(NQ > 0 ? NQ : 1), WANT_D> ps;
+    if (NQ > 0) ps.clear();
+    else
+      for (int k = 0; k <= MAXQ; ++k) dth[k] = 0.0;
+#pragma unroll
+    for (int j = 0; j < Tile::NJ; ++j) {
+      const long g = kc + (KT / 2) * wn + 16 * j + li;
+      const long gc = g < k_hi ? g : k_hi - 1;
+      const double kx = xyz[gc], ky = xyz[n_g + gc], kz = xyz[2 * n_g + gc];
+      const double wk = w[gc], rk = rho[gc], rtk = rhot[gc];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int bi = 16 * wm + lk + 4 * r;
+        double m[NCH];
+        pair_cotangents(acc, j, r, B, bi, wk, rk, rtk, m);
+        if (g >= k_hi || bt0 + bi >= bn) continue;
+        const double dx = B.xyz[0][bi] - kx, dy = B.xyz[1][bi] - ky, dz = B.xyz[2][bi] - kz;
+        if (NQ > 0) ps.add(cf, dx, dy, dz, m);
+        else pair_grad<NCH>(cf, gb, dx, dy, dz, m, dth);
+      }
     }
-    d4 acc[NCH][2][2];
-    m_tiles<NCH, NCH == 4>(Pb, rows_pad, bp, n_rows, xi, rho, rhot, w, n_g, n_mu, bt0, bn, kc,
-                           k_hi, Gs, As, acc);
-    // epilogue: the 16 pairs this lane holds, D[(l/16) + 4r][l%16] = M[bra][ket]
+    // over the wave in a fixed tree, then onto the wave's sums
+    const int ns = NQ > 0 ? NS : gb.n + gb.want_d;
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int k = 0; k < NS; ++k) {
+      if (k >= ns) break;
+      double v;
+      if (NQ == 0) v = dth[k < MAXQ + 1 ? k : 0];
+      else if (k < NQ) v = ps.S[k < NQ ? k : 0];
+      else if (k < 2 * NQ) v = ps.U[k >= NQ && k < 2 * NQ ? k - NQ : 0];
+      else v = k == 2 * NQ ? ps.S1 : ps.dd;
 #pragma unroll
-      for (int j = 0; j < 2; ++j)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int bi = 32 * wm + 16 * i + lk + 4 * r;
-          const int kj = 32 * wn + 16 * j + li;
-          if (bt0 + bi >= bn || kc + kj >= k_hi) continue;
-          double m[NCH];
-#pragma unroll
-          for (int c = 0; c < NCH; ++c) m[c] = acc[c][i][j][r];
-          pair_grad<NCH>(cf, gb, bxyz[0][bi] - kxyz[0][kj], bxyz[1][bi] - kxyz[1][kj],
-                         bxyz[2][bi] - kxyz[2][kj], m, dth);
-        }
-  }
-  // deterministic block reduction of the parameter partials (and dL/dd in slot n)
-  const int nout = gb.n + gb.want_d;
-  for (int k = 0; k < nout; ++k) {
-    double v = dth[k];
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
-    if (lane == 0) red[wave][k] = v;
+      for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
+      if (lane == 0) red[wave][k] += v;
+    }
   }
   __syncthreads();
+  const int nout = gb.n + gb.want_d;
   if (tid < nout) {
+    auto sum = [&](int k) { return (red[0][k] + red[1][k]) + (red[2][k] + red[3][k]); };
+    double v;
+    if (NQ > 0 && tid == gb.n) {
+      v = sum(2 * NQ + 1);   // dL/dd
+    } else if (NQ > 0) {
+      const int o = gb.o[tid];
+      v = o >= 2 ? o * (sum(o - 2) + sum(NQ + o - 1)) : o == 1 ? sum(2 * NQ) + sum(NQ) : 0.0;
+    } else {
+      v = sum(tid);
+    }
     const long blk = (long)blockIdx.y * gridDim.x + blockIdx.x;
-    partials[blk * (MAXQ + 1) + tid] = (red[0][tid] + red[1][tid]) + (red[2][tid] + red[3][tid]);
+    partials[blk * (MAXQ + 1) + tid] = v;
   }
 }
 
@@ -270,8 +428,8 @@ constexpr int ZS = BH_MAXTYPE * 64 + MAXQ + 1 + 1 + BH_MAXTYPE;
 template <int NT, bool LIN, bool NL>
 __device__ __forceinline__ void pair_grad_bh(const EECoef& cf, const BHTable* __restrict__ T,
                                              const double (*Cs)[BH_NP][BH_NP][BH_NO],
-                                             int nn, const double (*TB)[4][GT], int bi,
-                                             const double (*TA)[GT], int kj, double dx, double dy,
+                                             int nn, const double (*TB)[4][BT], int bi,
+                                             const double (*TA)[64], int kj, double dx, double dy,
                                              double dz, const double* m, double* z, double* zee,
                                              int omax_ee, double* znl) {
   const double r = sqrt(dx * dx + dy * dy + dz * dz);
@@ -411,38 +569,32 @@ __device__ __forceinline__ void pair_grad_bh(const EECoef& cf, const BHTable* __
 // (the separate two-type form crashes the device compiler).
 template <int NT, bool LIN, bool NL>
 __global__ __attribute__((amdgpu_flat_work_group_size(256, 256), amdgpu_waves_per_eu(1, 1)))
-void k_grad_pairs_bh(const double* __restrict__ Pb, long rows_pad, long bp, int n_rows,
+void k_grad_pairs_bh(const double* __restrict__ Pb, long rows_pad, long bp,
                      const double* __restrict__ xi, const double* __restrict__ rho,
                      const double* __restrict__ rhot, const double* __restrict__ w,
                      const double* __restrict__ xyz, long n_g, int n_mu, long b0, long bn,
                      EECoef cf, const BHTable* __restrict__ T, int omax_ee,
                      double* __restrict__ partials) {
-  constexpr int NCH = 4;
-  __shared__ double Gs[NCH][GK][GT + 1];
-  __shared__ double As[GK][GT + 1];
-  __shared__ double bxyz[3][GT];
-  __shared__ double kxyz[3][GT];
-  __shared__ double TB[BH_MAXNUC][4][GT];
-  __shared__ double TA[BH_MAXNUC][GT];
+  constexpr int NCH = 4, KT = 64;
+  using Tile = MTile<NCH, KT>;
+  __shared__ __align__(16) double sm[Tile::LDS];
+  __shared__ BraRows<NCH> B;
+  __shared__ double kxyz[3][KT];
+  __shared__ double TB[BH_MAXNUC][4][BT];
+  __shared__ double TA[BH_MAXNUC][KT];
   __shared__ double Cs[BH_MAXTYPE][BH_NP][BH_NP][BH_NO];
   __shared__ double red[4][ZS];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave >> 1, wn = wave & 1;
   const int li = lane & 15, lk = lane >> 4;
   const int nn = T->n_nuc;
-  const long bt0 = (long)blockIdx.x * GT;
-  const long per = ((n_g + KSEG - 1) / KSEG + GT - 1) / GT * GT;
+  const long bt0 = (long)blockIdx.x * BT;
+  const long per = ((n_g + KSEG - 1) / KSEG + KT - 1) / KT * KT;
   const long k_lo = (long)blockIdx.y * per;
   const long k_hi = k_lo + per < n_g ? k_lo + per : n_g;
-  if (tid < GT) {
-    long b = b0 + bt0 + tid;
-    if (b > b0 + bn - 1) b = b0 + bn - 1;
-    bxyz[0][tid] = xyz[b];
-    bxyz[1][tid] = xyz[n_g + b];
-    bxyz[2][tid] = xyz[2 * n_g + b];
-  }
-  for (int e = tid; e < nn * GT; e += 256) {
-    const int I = e / GT, bb = e % GT;
+  fill_bra_rows(B, xyz, n_g, b0, bt0, bn, Pb, rows_pad, bp, n_mu, tid);
+  for (int e = tid; e < nn * BT; e += 256) {
+    const int I = e / BT, bb = e % BT;
     long b = b0 + bt0 + bb;
     if (b > b0 + bn - 1) b = b0 + bn - 1;
     double v[4];
@@ -463,40 +615,40 @@ void k_grad_pairs_bh(const double* __restrict__ Pb, long rows_pad, long bp, int 
 #pragma unroll
   for (int k = 0; k < NZN; ++k) znl[k] = 0.0;
 
-  for (long kc = k_lo; kc < k_hi; kc += GT) {
-    __syncthreads();
-    if (tid < GT) {
+  Tile tile(sm, Pb, rows_pad, bp, n_mu, bt0, bn, xi, n_g, tid);
+  for (long kc = k_lo; kc < k_hi; kc += KT) {
+    __syncthreads();   // the previous tile's pairs are done with the ket tables
+    if (tid < KT) {
       long g = kc + tid;
       if (g > n_g - 1) g = n_g - 1;
       kxyz[0][tid] = xyz[g];
       kxyz[1][tid] = xyz[n_g + g];
       kxyz[2][tid] = xyz[2 * n_g + g];
     }
-    for (int e = tid; e < nn * GT; e += 256) {
-      const int I = e / GT, kk = e % GT;
+    for (int e = tid; e < nn * KT; e += 256) {
+      const int I = e / KT, kk = e % KT;
       long g = kc + kk;
       if (g > n_g - 1) g = n_g - 1;
       TA[I][kk] = bh_a(T, I, xyz[g], xyz[n_g + g], xyz[2 * n_g + g]);
     }
-    d4 acc[NCH][2][2];
-    m_tiles<NCH, NT == 1 && LIN && !NL>(Pb, rows_pad, bp, n_rows, xi, rho, rhot, w, n_g, n_mu, bt0, bn,
-                                 kc, k_hi, Gs, As, acc);
+    d4 acc[NCH][Tile::NJ];
+    tile.products(kc, acc);
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int j = 0; j < Tile::NJ; ++j) {
+      const int kj = (KT / 2) * wn + 16 * j + li;
+      const long g = kc + kj < k_hi ? kc + kj : k_hi - 1;
+      const double wk = w[g], rk = rho[g], rtk = rhot[g];
 #pragma unroll
-      for (int j = 0; j < 2; ++j)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int bi = 32 * wm + 16 * i + lk + 4 * r;
-          const int kj = 32 * wn + 16 * j + li;
-          if (bt0 + bi >= bn || kc + kj >= k_hi) continue;
-          double mv[NCH];
-#pragma unroll
-          for (int c = 0; c < NCH; ++c) mv[c] = acc[c][i][j][r];
-          pair_grad_bh<NT, LIN, NL>(cf, T, Cs, nn, TB, bi, TA, kj, bxyz[0][bi] - kxyz[0][kj],
-                           bxyz[1][bi] - kxyz[1][kj], bxyz[2][bi] - kxyz[2][kj], mv, z, zee,
-                           omax_ee, znl);
-        }
+      for (int r = 0; r < 4; ++r) {
+        const int bi = 16 * wm + lk + 4 * r;
+        double mv[NCH];
+        pair_cotangents(acc, j, r, B, bi, wk, rk, rtk, mv);
+        if (bt0 + bi >= bn || kc + kj >= k_hi) continue;
+        pair_grad_bh<NT, LIN, NL>(cf, T, Cs, nn, TB, bi, TA, kj, B.xyz[0][bi] - kxyz[0][kj],
+                         B.xyz[1][bi] - kxyz[1][kj], B.xyz[2][bi] - kxyz[2][kj], mv, z, zee,
+                         omax_ee, znl);
+      }
+    }
   }
   // deterministic block reduction: [NT * 64 Z entries][MAXQ + 1 Zee entries][1 + NT nonlinear]
   __syncthreads();
@@ -534,13 +686,21 @@ __global__ void k_bh_params(const double* __restrict__ zsum, const BHParamMap* _
   out[p] = q.scale * (zsum[q.i1] + (q.i2 >= 0 ? zsum[q.i2] : 0.0));
 }
 
-__global__ void k_sum_partials(const double* __restrict__ partials, long nblk, int n, int stride,
-                               double* __restrict__ out) {
-  const int k = blockIdx.x * 256 + threadIdx.x;
-  if (k >= n) return;
-  double s = 0.0;
-  for (long b = 0; b < nblk; ++b) s += partials[b * stride + k];
-  out[k] = s;
+// out[k] = the sum of partials[.][k]: one workgroup per k, strided sums and a fixed tree (one
+// thread per k walked the blocks one load at a time: 0.7 ms for 1,456 blocks)
+__global__ __launch_bounds__(256) void k_sum_partials(const double* __restrict__ partials,
+                                                      long nblk, int stride,
+                                                      double* __restrict__ out) {
+  __shared__ double s[256];
+  const int k = blockIdx.x, tid = threadIdx.x;
+  double v = 0.0;
+  for (long b = tid; b < nblk; b += 256) v += partials[b * stride + k];
+  s[tid] = v;
+  for (int off = 128; off > 0; off >>= 1) {
+    __syncthreads();
+    if (tid < off) s[tid] += s[tid + off];
+  }
+  if (tid == 0) out[k] = s[0];
 }
 
 __global__ void k_sym(const double* __restrict__ a, long n, double* __restrict__ s) {
@@ -603,7 +763,7 @@ static GradLayout layout_grad(Arena& ar, int64_t n_g, int n_mu, int n_params, ui
   L.bp = n_g < GSUPER ? ((n_g + 63) / 64) * 64 : GSUPER;
   L.rows_pad = ((n_mu + 2 + 63) / 64) * 64;
   L.nsb = (int)cdiv(n_g, L.bp);
-  L.nblk = (long)cdiv(L.bp, GT) * KSEG;
+  L.nblk = (long)cdiv(L.bp, BT) * KSEG;
   L.piv = ar.take<long>(n_mu);
   L.G = ar.take<double>(n_mu);
   L.rhot = ar.take<double>(n_g);
@@ -785,13 +945,13 @@ extern "C" xtc_status xtc_grad(const xtc_grid* grid, const xtc_correlator* corr,
                          (const double*)L.F, (const double*)L.Pd, L.rows_pad, L.bp, n_mu, bn);
       XTC_CHECK_LAUNCH();
     }
-    dim3 gridp(cdiv(bn, GT), KSEG);
+    const dim3 gridp(cdiv(bn, BT), KSEG);
     const int stride = bh ? ZS : MAXQ + 1;
     double* part = L.partials + (long)sb * L.nblk * stride;
     if (bh) {
 #define XTC_LAUNCH_BH(NTV, LINV, NLV)                                                           \
   hipLaunchKernelGGL((k_grad_pairs_bh<NTV, LINV, NLV>), gridp, dim3(256), 0, st,                 \
-                     (const double*)L.Pb, L.rows_pad, L.bp, n_mu + 2, xi, rho,                   \
+                     (const double*)L.Pb, L.rows_pad, L.bp, xi, rho,                             \
                      (const double*)L.rhot, grid->w, grid->xyz, n_g, n_mu, b0, bn, cf,           \
                      (const BHTable*)L.bh, omax_ee, part)
       if (bt.n_types == 1) {
@@ -807,14 +967,22 @@ extern "C" xtc_status xtc_grad(const xtc_grid* grid, const xtc_correlator* corr,
       }
 #undef XTC_LAUNCH_BH
     }
-    else if (L.nch == 4)
-      hipLaunchKernelGGL(k_grad_pairs<4>, gridp, dim3(256), 0, st, (const double*)L.Pb, L.rows_pad,
-                         L.bp, n_mu + 2, xi, rho, (const double*)L.rhot, grid->w, grid->xyz, n_g,
-                         n_mu, b0, bn, cf, gb, part);
-    else
-      hipLaunchKernelGGL(k_grad_pairs<5>, gridp, dim3(256), 0, st, (const double*)L.Pb, L.rows_pad,
-                         L.bp, n_mu + 2, xi, rho, (const double*)L.rhot, grid->w, grid->xyz, n_g,
-                         n_mu, b0, bn, cf, gb, part);
+    else {
+      auto go = [&](auto nch, auto nq, auto want_d) {
+        hipLaunchKernelGGL((k_grad_pairs<nch.value, nq.value, want_d.value>), gridp, dim3(256), 0, st,
+                           (const double*)L.Pb, L.rows_pad, L.bp, xi, rho, (const double*)L.rhot,
+                           grid->w, grid->xyz, n_g, n_mu, b0, bn, cf, gb, part);
+      };
+      // power sums for four channels; the Laplacian's terms take the general loop
+      auto four = [&](auto nq) {
+        if (dd) go(std::integral_constant<int, 4>{}, nq, std::true_type{});
+        else go(std::integral_constant<int, 4>{}, nq, std::false_type{});
+      };
+      if (L.nch == 5)
+        go(std::integral_constant<int, 5>{}, std::integral_constant<int, 0>{}, std::false_type{});
+      else if (gb.omax <= 8) four(std::integral_constant<int, 8>{});
+      else four(std::integral_constant<int, MAXQ>{});
+    }
     XTC_CHECK_LAUNCH();
     // unused block slots of a short last super-block stay zero
     if ((long)gridp.x * KSEG < L.nblk)
@@ -822,8 +990,8 @@ extern "C" xtc_status xtc_grad(const xtc_grid* grid, const xtc_correlator* corr,
                              sizeof(double) * (L.nblk - (long)gridp.x * KSEG) * stride, st));
   }
   if (bh) {
-    hipLaunchKernelGGL(k_sum_partials, dim3(cdiv(ZS, 256)), dim3(256), 0, st,
-                       (const double*)L.partials, (long)nsb * L.nblk, ZS, ZS, L.zsum);
+    hipLaunchKernelGGL(k_sum_partials, dim3(ZS), dim3(256), 0, st, (const double*)L.partials,
+                       (long)nsb * L.nblk, ZS, L.zsum);
     XTC_CHECK_LAUNCH();
     hipLaunchKernelGGL(k_bh_params, dim3(cdiv(n_params, 256)), dim3(256), 0, st,
                        (const double*)L.zsum, (const BHParamMap*)L.pmap, n_params, dtheta);
@@ -831,8 +999,8 @@ extern "C" xtc_status xtc_grad(const xtc_grid* grid, const xtc_correlator* corr,
       XTC_HIP(hipMemcpyAsync(dd, L.zsum + bt.n_types * 64 + MAXQ + 1,
                              sizeof(double) * (1 + bt.n_types), hipMemcpyDeviceToDevice, st));
   } else {
-    hipLaunchKernelGGL(k_sum_partials, dim3(1), dim3(64), 0, st, (const double*)L.partials,
-                       (long)nsb * L.nblk, gb.n + gb.want_d, MAXQ + 1, L.zsum);
+    hipLaunchKernelGGL(k_sum_partials, dim3(gb.n + gb.want_d), dim3(256), 0, st,
+                       (const double*)L.partials, (long)nsb * L.nblk, MAXQ + 1, L.zsum);
     XTC_CHECK_LAUNCH();
     XTC_HIP(hipMemcpyAsync(dtheta, L.zsum, sizeof(double) * gb.n, hipMemcpyDeviceToDevice, st));
     if (dd) XTC_HIP(hipMemcpyAsync(dd, L.zsum + gb.n, sizeof(double), hipMemcpyDeviceToDevice, st));
