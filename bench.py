@@ -789,7 +789,7 @@ def assembly_cpu_baseline(wl, n_p=1):
     t0 = time.perf_counter()
     oasm.w_panel(phi, u1, u3, D1, D4, X, 0, n_p)
     dt = time.perf_counter() - t0
-    flops = 2.0 * n_p * n ** 3 * 4 * n_mu
+    flops = 2.0 * n_p * n ** 3 * 2 * n_mu
     return {"value": round(flops / dt / 1e12, 6), "unit": "TFLOP/s", "cores": cores, "kind": "oracle",
             "sample": f"W panel of {n_p} of {n} orbitals, N_mu={n_mu}; {dt:.1f} s"}
 

@@ -11,29 +11,34 @@
 // diagonal d (ties to the lowest index), and one set of FP64 matrix-core GEMMs
 // forms their columns against every grid point,
 //   R[c][g] = S(g, c) - sum_{l < mu0} L[l][g] L[l][c],
-// from the orbitals at the candidates and the factor rows gathered there. Each
-// step of the batch then takes the exact argmax of d over all points; while that
-// pivot g* is a candidate, its factor row needs only R[g*] and the rows made in
-// this batch,
+// from the orbitals at the candidates and the factor rows gathered there. While the
+// exact argmax g* of d over all points is a candidate, its factor row needs only R[g*]
+// and the rows made in this batch,
 //   L[mu][g] = (R[g*][g] - sum_{mu0 <= l < mu} L[l][g] L[l][g*]) / sqrt(d_g*),
 // and the first pivot outside C ends the batch (the next batch's C holds it, as
 // the largest d). The selected points, the stop rules and the fused order are
 // those of the plain algorithm; the sums are grouped differently, so the factor
 // agrees with a plain step's to rounding.
 //
-// One step = two launches:
-//   k_pick   (one block)  reduces the per-block (max d, lowest index) partials,
-//                         applies the rank-deficiency stop, ends the batch when the
-//                         pivot is not a candidate, records g*, and gathers the
-//                         batch's factor entries L[mu0..mu)[g*];
-//   k_column (grid)       forms the new factor row from R, updates d and emits new
-//                         partials.
-// All state (d, L, partials, control word) lives in the workspace; the host
-// synchronises once or twice per batch to see how far it went. Ties in the argmax
-// go to the lowest grid index; the reduction order is fixed, so repeated runs
-// select identical pivots.
+// The steps of a batch are not launched one by one (a pick and a column launch of ~4 us
+// each, whatever their work): the greedy sequence among the candidates needs only the
+// 64 x 64 values R[c][c'] and is made in advance, then replayed at every point:
+//   k_top_local / k_top_merge  the previous batch's accepted rows taken off d, and the
+//                  64 largest d with their points;
+//   k_plan   (one block)  the greedy sequence among the candidates: pivots g_t, their d_t
+//                  and the factor entries L[l][g_t], up to NPLAN steps or the
+//                  rank-deficiency stop;
+//   k_replay (grid)  the factor rows of all planned steps at every point; a point whose
+//                  d exceeds d_t before step t marks that step: the argmax was not g_t.
+// The steps before the first marked one are the plain algorithm's; the host, which reads
+// the plan and the marks once per batch, records them. Ties go to the lowest grid index
+// and every sum has a fixed order, so repeated runs select identical pivots.
+// 1,733 steps of an eight-atom chain (46,560 points) in 79 batches: 34.2 -> 17.1 ms, of
+// which the products 7.1, plan and replay 4.5, candidate search 2.0 (9.0 with LDS sorts).
+#include <cstddef>
 #include <cstdio>
 #include <cstdlib>
+#include <utility>
 #include "common.hpp"
 #include "plans.hpp"
 #include "timing.hpp"
@@ -43,20 +48,19 @@ namespace xtc {
 constexpr int PIV_BLOCK = 256;
 constexpr double RANK_TOL = 1e-14;
 constexpr int NCAND = 64;      // candidates per batch (one 64-row GEMM tile)
-constexpr int TOP_SEG = 1024;  // entries sorted per block of the candidate search
+constexpr int NPLAN = 48;      // steps planned per batch: two factor entries per VGPR pair in
+                               // the replay, and about twice the 20-30 steps a batch accepts
+constexpr int TOP_PTS = 512;   // points per block of the candidate search
 
-struct PivCtl {
-  long gstar;
-  double dstar;
-  double d0max;
-  int step;     // pivots recorded so far in the current channel
-  int stop;     // 0 running, 1 rank deficient, 2 fused target reached
-  int union_n;  // |grad pivots U scalar pivots|
-  int target;   // fused target (scalar channel) or 0
-  int mu0;      // pivots recorded before the current batch
-  int slot;     // candidate slot of the current pivot
-  int bend;     // 1: the current batch has ended (a pivot outside its candidates)
-  int stamp;    // current batch number (candidate stamps are stamp << 6 | slot)
+// The planned steps of a batch (k_plan) and what the replay found (k_replay).
+struct PivPlan {
+  int steps;              // planned steps T
+  int stop;               // 1: the best candidate after them is at or below the rank tolerance
+  int mark[NPLAN + 1];    // step t (or the stop after T steps): some point's d is larger
+  int slot[NPLAN];        // candidate slot of step t's pivot
+  long g[NPLAN + 1];      // step t's pivot (entry T: the best candidate left at a stop)
+  double d[NPLAN + 1];    // its residual diagonal before the step
+  double lstar[NPLAN][NPLAN];   // lstar[t][l] = L[mu0 + l][g_t], l < t
 };
 
 struct Cand {
@@ -70,35 +74,12 @@ __device__ __forceinline__ Cand better(Cand a, Cand b) {
   return a.g <= b.g ? a : b;
 }
 
-__device__ Cand block_argmax(Cand c) {
-  __shared__ double sd[PIV_BLOCK / 64];
-  __shared__ long sg[PIV_BLOCK / 64];
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) {
-    Cand o;
-    o.d = __shfl_down(c.d, off, 64);
-    o.g = __shfl_down(c.g, off, 64);
-    c = better(c, o);
-  }
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  __syncthreads();
-  if (lane == 0) {
-    sd[wave] = c.d;
-    sg[wave] = c.g;
-  }
-  __syncthreads();
-  Cand r{sd[0], sg[0]};
-  for (int w = 1; w < PIV_BLOCK / 64; ++w) r = better(r, Cand{sd[w], sg[w]});
-  return r;
-}
-
 // channel: 0 scalar, 1 gradient
 __global__ __launch_bounds__(PIV_BLOCK) void k_diag(const double* __restrict__ phi4,
                                                     const double* __restrict__ w, long n_g,
-                                                    int n_orb, int channel, double* __restrict__ d,
-                                                    double* __restrict__ pd, long* __restrict__ pg) {
+                                                    int n_orb, int channel,
+                                                    double* __restrict__ d) {
   long g = (long)blockIdx.x * PIV_BLOCK + threadIdx.x;
-  Cand c{-1.0, 0x7fffffffffffffffL};
   if (g < n_g) {
     double n2 = 0.0, g2 = 0.0;
     for (int p = 0; p < n_orb; ++p) {
@@ -116,185 +97,266 @@ __global__ __launch_bounds__(PIV_BLOCK) void k_diag(const double* __restrict__ p
       dd = w[g] * w[g] * n2 * g2;
     }
     d[g] = dd;
-    c = Cand{dd, g};
-  }
-  c = block_argmax(c);
-  if (threadIdx.x == 0) {
-    pd[blockIdx.x] = c.d;
-    pg[blockIdx.x] = c.g;
-  }
-}
-
-__global__ __launch_bounds__(PIV_BLOCK) void k_pick(const double* __restrict__ pd,
-                                                    const long* __restrict__ pg, int nparts,
-                                                    PivCtl* ctl, long* __restrict__ piv,
-                                                    const double* __restrict__ L, long n_g,
-                                                    double* __restrict__ lstar,
-                                                    unsigned char* __restrict__ mark,
-                                                    const int* __restrict__ cslot, int mode,
-                                                    int first) {
-  // mode 0: gradient channel (marks its pivots); mode 1: scalar channel (fills the union)
-  __shared__ int s_done;
-  __shared__ long s_g;
-  __shared__ int s_step, s_mu0;
-  Cand c{-1.0, 0x7fffffffffffffffL};
-  for (int i = threadIdx.x; i < nparts; i += PIV_BLOCK) c = better(c, Cand{pd[i], pg[i]});
-  c = block_argmax(c);
-  if (threadIdx.x == 0) {
-    if (first) {
-      ctl->d0max = c.d;
-      ctl->stop = 0;
-      ctl->step = 0;
-    }
-    int stop = ctl->stop;   // 1: rank deficient, 2: fused target complete
-    int bend = ctl->bend;   // the batch has ended
-    const int step = ctl->step;
-    if (!stop && !bend) {
-      const int sl = cslot[c.g];
-      if (!(c.d > RANK_TOL * ctl->d0max)) {
-        stop = 1;
-      } else if ((sl >> 6) != ctl->stamp) {
-        bend = 1;            // not a candidate: the next batch starts from this point
-      } else {
-        piv[step] = c.g;
-        ctl->gstar = c.g;
-        ctl->dstar = c.d;
-        ctl->slot = sl & (NCAND - 1);
-        ctl->step = step + 1;
-        if (mode == 0) {
-          mark[c.g] = 1;
-        } else if (!mark[c.g]) {
-          ctl->union_n += 1;
-          // the completing pivot is recorded; no further column is needed
-          if (ctl->union_n >= ctl->target) stop = 2;
-        }
-      }
-    }
-    ctl->stop = stop;
-    ctl->bend = bend;
-    s_done = stop || bend;
-    s_step = step;
-    s_mu0 = ctl->mu0;
-    s_g = c.g;
-  }
-  __syncthreads();
-  if (s_done) return;
-  const long gs = s_g;
-  for (int l = threadIdx.x; l < s_step - s_mu0; l += PIV_BLOCK)
-    lstar[l] = L[(long)(s_mu0 + l) * n_g + gs];
-}
-
-// dot(x[i * stride], y[i]) over i < n with sixteen loads in flight and four
-// accumulators combined in a fixed order (the column is memory-bound; a single
-// dependent chain would leave one load outstanding per wave)
-__device__ __forceinline__ double strided_dot(const double* __restrict__ x, long stride,
-                                              const double* __restrict__ y, int n) {
-  double a[4] = {0.0, 0.0, 0.0, 0.0};
-  int i = 0;
-  for (; i + 16 <= n; i += 16) {
-    double v[16];
-#pragma unroll
-    for (int u = 0; u < 16; ++u) v[u] = x[(long)(i + u) * stride];
-#pragma unroll
-    for (int u = 0; u < 16; ++u) a[u & 3] += v[u] * y[i + u];
-  }
-  for (; i < n; ++i) a[0] += x[(long)i * stride] * y[i];
-  return (a[0] + a[1]) + (a[2] + a[3]);
-}
-
-// The new factor row from the candidate's column R[slot] and the batch's earlier rows.
-__global__ __launch_bounds__(PIV_BLOCK) void k_column(const double* __restrict__ R, long n_g,
-                                                      double* __restrict__ L,
-                                                      const double* __restrict__ lstar,
-                                                      const PivCtl* __restrict__ ctl,
-                                                      double* __restrict__ d,
-                                                      double* __restrict__ pd,
-                                                      long* __restrict__ pg) {
-  __shared__ double sl[NCAND];
-  if (ctl->stop || ctl->bend) return;
-  const int mu = ctl->step - 1, mu0 = ctl->mu0, nb = mu - mu0;
-  const long gs = ctl->gstar;
-  const double inv = 1.0 / sqrt(ctl->dstar);
-  const double* Rc = R + (long)ctl->slot * n_g;
-  for (int i = threadIdx.x; i < nb; i += PIV_BLOCK) sl[i] = lstar[i];
-  __syncthreads();
-  const long g = (long)blockIdx.x * PIV_BLOCK + threadIdx.x;
-  Cand c{-1.0, 0x7fffffffffffffffL};
-  if (g < n_g) {
-    const double acc = strided_dot(L + (long)mu0 * n_g + g, n_g, sl, nb);
-    const double col = (Rc[g] - acc) * inv;
-    L[(long)mu * n_g + g] = col;
-    double dn = d[g] - col * col;
-    dn = dn > 0.0 ? dn : 0.0;
-    if (g == gs) dn = 0.0;
-    d[g] = dn;
-    c = Cand{dn, g};
-  }
-  c = block_argmax(c);
-  if (threadIdx.x == 0) {
-    pd[blockIdx.x] = c.d;
-    pg[blockIdx.x] = c.g;
   }
 }
 
 // --- the candidate search: the NCAND best (d, index) pairs -----------------------
-// Each block sorts TOP_SEG entries (bitonic, best first: larger d, then lower index)
-// and keeps its NCAND best; repeated over the outputs until one block remains.
-// in_g == nullptr: the entries are d[0..n_in) with their own indices.
-__global__ __launch_bounds__(256) void k_top_sort(const double* __restrict__ in_d,
-                                                  const long* __restrict__ in_g, long n_in,
-                                                  double* __restrict__ out_d,
-                                                  long* __restrict__ out_g) {
-  __shared__ double sd[TOP_SEG];
-  __shared__ long sg[TOP_SEG];
-  const long base = (long)blockIdx.x * TOP_SEG;
-  for (int i = threadIdx.x; i < TOP_SEG; i += 256) {
-    const long k = base + i;
-    if (k < n_in) {
-      sd[i] = in_d[k];
-      sg[i] = in_g ? in_g[k] : k;
-    } else {
-      sd[i] = -1.0;   // below every residual diagonal (d >= 0)
-      sg[i] = 0x7fffffffffffffffL;
+// A wave holds one sorted list of 64, best first (larger d, then lower index).
+constexpr Cand NO_CAND{-1.0, 0x7fffffffffffffffL};   // below every residual diagonal (d >= 0)
+
+__device__ __forceinline__ Cand shfl_cand(Cand c, int lane) {
+  return Cand{__shfl(c.d, lane, 64), __shfl(c.g, lane, 64)};
+}
+
+// one compare-exchange with lane ^ j; the lower lane keeps the better entry if best_first
+__device__ __forceinline__ Cand exchange(Cand c, int lane, int j, bool best_first) {
+  const Cand o = shfl_cand(c, lane ^ j);
+  const bool other = o.d > c.d || (o.d == c.d && o.g < c.g);
+  return other == (((lane & j) == 0) == best_first) ? o : c;
+}
+
+__device__ __forceinline__ Cand sort64(Cand c, int lane) {
+#pragma unroll
+  for (int k = 2; k <= 64; k <<= 1)
+#pragma unroll
+    for (int j = k >> 1; j > 0; j >>= 1) c = exchange(c, lane, j, (lane & k) == 0);
+  return c;
+}
+
+// the 64 best of two sorted lists, sorted
+__device__ __forceinline__ Cand merge64(Cand a, Cand b, int lane) {
+  a = better(a, shfl_cand(b, 63 - lane));
+#pragma unroll
+  for (int j = 32; j > 0; j >>= 1) a = exchange(a, lane, j, true);
+  return a;
+}
+
+// whether any entry of list c would enter the sorted list `kept`
+__device__ __forceinline__ bool enters(Cand kept, Cand c) {
+  const Cand last = shfl_cand(kept, 63);
+  return __any(c.d > last.d || (c.d == last.d && c.g < last.g));
+}
+
+// merges the lists of a block's waves (W a power of two) in LDS; wave 0 returns the result
+template <int W>
+__device__ __forceinline__ Cand block_merge(Cand c, double (*sd)[64], long (*sg)[64], int lane,
+                                            int wave) {
+  for (int h = W / 2; h > 0; h >>= 1) {
+    if (wave >= h && wave < 2 * h) {
+      sd[wave][lane] = c.d;
+      sg[wave][lane] = c.g;
     }
+    __syncthreads();
+    if (wave < h) c = merge64(c, Cand{sd[wave + h][lane], sg[wave + h][lane]}, lane);
+    __syncthreads();
   }
-  for (int k = 2; k <= TOP_SEG; k <<= 1)
-    for (int j = k >> 1; j > 0; j >>= 1) {
-      __syncthreads();
-      for (int i = threadIdx.x; i < TOP_SEG; i += 256) {
-        const int p = i ^ j;
-        if (p <= i) continue;
-        const double di = sd[i], dp = sd[p];
-        const long gi = sg[i], gp = sg[p];
-        const bool p_better = dp > di || (dp == di && gp < gi);
-        const bool best_first = (i & k) == 0;
-        if (p_better == best_first) {
-          sd[i] = dp; sg[i] = gp;
-          sd[p] = di; sg[p] = gi;
+  return c;
+}
+
+// Points [TOP_PTS blockIdx.x, ...): the previous batch's n_acc accepted rows L[mu0 ..] are
+// taken off d, then the 64 best points of the block.
+__global__ __launch_bounds__(256) void k_top_local(double* __restrict__ d, long n_g,
+                                                   const double* __restrict__ L, long mu0,
+                                                   int n_acc, const PivPlan* __restrict__ plan,
+                                                   double* __restrict__ out_d,
+                                                   long* __restrict__ out_g) {
+  __shared__ double sd[4][64];
+  __shared__ long sg[4][64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  Cand kept = NO_CAND;
+  for (int i = 0; i < TOP_PTS / 256; ++i) {
+    const long g = (long)blockIdx.x * TOP_PTS + 256 * i + threadIdx.x;
+    Cand c = NO_CAND;
+    if (g < n_g) {
+      double dn = d[g];
+      if (n_acc > 0) {
+        for (int t0 = 0; t0 < n_acc; t0 += 8) {   // eight rows' loads in flight
+          double col[8];
+#pragma unroll
+          for (int u = 0; u < 8; ++u)
+            col[u] = L[(mu0 + (t0 + u < n_acc ? t0 + u : n_acc - 1)) * n_g + g];
+#pragma unroll
+          for (int u = 0; u < 8; ++u) {
+            if (t0 + u >= n_acc) break;
+            dn = dn - col[u] * col[u];
+            dn = dn > 0.0 ? dn : 0.0;
+            if (g == plan->g[t0 + u]) dn = 0.0;
+          }
         }
+        d[g] = dn;
       }
+      c = Cand{dn, g};
     }
-  __syncthreads();
-  if (threadIdx.x < NCAND) {
-    out_d[(long)blockIdx.x * NCAND + threadIdx.x] = sd[threadIdx.x];
-    out_g[(long)blockIdx.x * NCAND + threadIdx.x] = sg[threadIdx.x];
+    if (i == 0) kept = sort64(c, lane);
+    else if (enters(kept, c)) kept = merge64(kept, sort64(c, lane), lane);
+  }
+  kept = block_merge<4>(kept, sd, sg, lane, wave);
+  if (wave == 0) {
+    out_d[(long)blockIdx.x * NCAND + lane] = kept.d;
+    out_g[(long)blockIdx.x * NCAND + lane] = kept.g;
   }
 }
 
-// Opens a batch: stamps the candidates, records mu0 and clears the end flag.
-__global__ void k_batch_begin(const double* __restrict__ cd, const long* __restrict__ cg,
-                              long n_g, int* __restrict__ cslot, int stamp,
-                              long* __restrict__ cand, PivCtl* ctl) {
-  const int m = threadIdx.x;
-  const long g = cg[m];
-  const bool ok = cd[m] >= 0.0 && g >= 0 && g < n_g;
-  cand[m] = ok ? g : -1;
-  if (ok) cslot[g] = (stamp << 6) | m;
-  if (m == 0) {
-    ctl->mu0 = ctl->step;
-    ctl->bend = 0;
-    ctl->stamp = stamp;
+// The 64 best of the blocks' lists: the candidates, best first (-1 where there are fewer).
+__global__ __launch_bounds__(1024) void k_top_merge(const double* __restrict__ in_d,
+                                                    const long* __restrict__ in_g, int n_lists,
+                                                    long n_g, long* __restrict__ cand) {
+  __shared__ double sd[16][64];
+  __shared__ long sg[16][64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  Cand kept = NO_CAND;
+  for (int l = wave; l < n_lists; l += 16) {
+    const Cand c{in_d[(long)l * NCAND + lane], in_g[(long)l * NCAND + lane]};
+    if (enters(kept, c)) kept = merge64(kept, c, lane);
   }
+  kept = block_merge<16>(kept, sd, sg, lane, wave);
+  if (wave == 0) cand[lane] = kept.g >= 0 && kept.g < n_g ? kept.g : -1;
+}
+
+// Every factor entry, planned or replayed, sums x[l] y[l], l < t, in one order: four
+// accumulators over whole groups of sixteen and the rest in the first.
+template <class F, int... I>
+__device__ __forceinline__ void for_each_int(F&& f, std::integer_sequence<int, I...>) {
+  (f(std::integral_constant<int, I>{}), ...);
+}
+
+// max over the wave by row shifts and broadcasts (no LDS round trips); NaNs are passed over
+__device__ __forceinline__ double wave_max(double v) {
+  auto shifted = [](double x, auto ctrl) {
+    const long b = __builtin_bit_cast(long, x);
+    const int lo = __builtin_amdgcn_update_dpp((int)b, (int)b, ctrl.value, 0xf, 0xf, false);
+    const int hi = __builtin_amdgcn_update_dpp((int)(b >> 32), (int)(b >> 32), ctrl.value, 0xf, 0xf, false);
+    return __builtin_bit_cast(double, (long)(unsigned)lo | ((long)hi << 32));
+  };
+  v = fmax(v, shifted(v, std::integral_constant<int, 0x111>{}));   // row_shr 1, 2, 4, 8
+  v = fmax(v, shifted(v, std::integral_constant<int, 0x112>{}));
+  v = fmax(v, shifted(v, std::integral_constant<int, 0x114>{}));
+  v = fmax(v, shifted(v, std::integral_constant<int, 0x118>{}));
+  v = fmax(v, shifted(v, std::integral_constant<int, 0x142>{}));   // row_bcast 15, 31
+  v = fmax(v, shifted(v, std::integral_constant<int, 0x143>{}));
+  const long b = __builtin_bit_cast(long, v);
+  const int lo = __builtin_amdgcn_readlane((int)b, 63), hi = __builtin_amdgcn_readlane((int)(b >> 32), 63);
+  return __builtin_bit_cast(double, (long)(unsigned)lo | ((long)hi << 32));
+}
+
+// The greedy sequence among the candidates, at most `lim` steps; d0max <= 0: the channel's
+// first batch, whose first pivot sets the rank tolerance. One wave, compile-time steps.
+__global__ __launch_bounds__(256) void k_plan(const double* __restrict__ R,
+                                              const double* __restrict__ d, long n_g,
+                                              const long* __restrict__ cand, int lim,
+                                              double d0max, PivPlan* __restrict__ plan) {
+  __shared__ double Rc[NCAND][NCAND + 1];
+  __shared__ double Lb[NPLAN][NCAND + 1];
+  for (int e = threadIdx.x; e < NCAND * NCAND; e += 256) {
+    const long g = cand[e % NCAND];
+    Rc[e / NCAND][e % NCAND] = g >= 0 ? R[(long)(e / NCAND) * n_g + g] : 0.0;
+  }
+  if (threadIdx.x <= NPLAN) plan->mark[threadIdx.x] = 0;
+  __syncthreads();
+  if (threadIdx.x >= 64) return;
+  const int lane = threadIdx.x;
+  const long gc = cand[lane];
+  double dc = gc >= 0 ? d[gc] : -1.0;
+  double col[NPLAN];
+  int T = 0, stop = 0;
+  auto step = [&](auto tc) {
+    constexpr int t = tc.value;
+    if (t >= lim || stop) return;
+    const double bd = wave_max(dc);
+    // the lowest grid index among the lanes that hold the maximum (one, but for ties)
+    unsigned long hold = __ballot(dc == bd);
+    int bs = hold ? __builtin_ctzl(hold) : 0;   // none: NaN, which stops below
+    long bg = __shfl(gc, bs, 64);
+    for (hold &= hold - 1; hold; hold &= hold - 1) {
+      const int o = __builtin_ctzl(hold);
+      const long og = __shfl(gc, o, 64);
+      if (og < bg) {
+        bg = og;
+        bs = o;
+      }
+    }
+    bs = __builtin_amdgcn_readfirstlane(bs);
+    if (t == 0 && d0max <= 0.0) d0max = bd;
+    if (lane == 0) {
+      plan->g[t] = bg;
+      plan->d[t] = bd;
+    }
+    if (!(bd > RANK_TOL * d0max)) {
+      stop = 1;
+      return;
+    }
+    if (lane == 0) plan->slot[t] = bs;
+    if (lane < t) plan->lstar[t][lane] = Lb[lane][bs];
+    const double inv = 1.0 / sqrt(bd);
+    double a[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int l = 0; l < t; ++l) {
+      const int q = l < (t & ~15) ? l & 3 : 0;
+      a[q] = fma(col[l], Lb[l][bs], a[q]);
+    }
+    col[t] = (Rc[bs][lane] - ((a[0] + a[1]) + (a[2] + a[3]))) * inv;
+    Lb[t][lane] = col[t];
+    __builtin_amdgcn_s_waitcnt(0xc07f);   // one wave: the store is done before the next reads
+    double dn = dc - col[t] * col[t];
+    dn = dn > 0.0 ? dn : 0.0;
+    if (gc >= 0) dc = lane == bs ? 0.0 : dn;
+    T = t + 1;
+  };
+  for_each_int(step, std::make_integer_sequence<int, NPLAN>{});
+  if (lane == 0) {
+    plan->steps = T;
+    plan->stop = stop;
+  }
+}
+
+// The planned steps at every point: the factor rows L[mu0 + t], and a mark on each step
+// before which the point's d is larger than the planned pivot's.
+__global__ __launch_bounds__(PIV_BLOCK) void k_replay(const double* __restrict__ R, long n_g,
+                                                      const double* __restrict__ d,
+                                                      double* __restrict__ L, long mu0,
+                                                      PivPlan* __restrict__ plan_rw,
+                                                      const PivPlan* __restrict__ plan) {
+  const long g = (long)blockIdx.x * PIV_BLOCK + threadIdx.x;
+  const bool in = g < n_g;
+  const long gg = in ? g : n_g - 1;
+  double dn = d[gg];
+  double col[NPLAN];
+  const int T = plan->steps, stop = plan->stop;
+  constexpr int AHEAD = 8;   // R loads in flight ahead of their step
+  double r[AHEAD];
+  auto request = [&](int t) {
+    return R[(long)plan->slot[t < T ? t : (T > 0 ? T - 1 : 0)] * n_g + gg];
+  };
+  if (T > 0)
+#pragma unroll
+    for (int t = 0; t < AHEAD; ++t) r[t] = request(t);
+  auto check = [&](int t) {
+    const double dt = plan->d[t];
+    const long gt = plan->g[t];
+    if (__any(in && (dn > dt || (dn == dt && g < gt))) && (threadIdx.x & 63) == 0)
+      plan_rw->mark[t] = 1;
+  };
+  auto step = [&](auto tc) {   // compile-time t: the point's factor entries stay in registers
+    constexpr int t = tc.value;
+    if (t >= T) return;
+    if (t > 0) check(t);   // the first pivot is the largest d by construction
+    const double rt = r[t % AHEAD];
+    r[t % AHEAD] = request(t + AHEAD);
+    const double inv = 1.0 / sqrt(plan->d[t]);
+    double a[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int l = 0; l < t; ++l) {
+      const int q = l < (t & ~15) ? l & 3 : 0;
+      a[q] = fma(col[l], plan->lstar[t][l], a[q]);
+    }
+    col[t] = (rt - ((a[0] + a[1]) + (a[2] + a[3]))) * inv;
+    if (in) L[(mu0 + t) * n_g + g] = col[t];
+    dn = dn - col[t] * col[t];
+    dn = dn > 0.0 ? dn : 0.0;
+    if (g == plan->g[t]) dn = 0.0;
+  };
+  for_each_int(step, std::make_integer_sequence<int, NPLAN>{});
+  if (stop && T > 0) check(T);
 }
 
 // The orbital values and factor entries at the candidates, candidate-major:
@@ -344,39 +406,26 @@ __global__ __launch_bounds__(256) void k_pair_values(double* __restrict__ R,
 }
 
 struct SelLayout {
-  double* d; double* L; double* pd; long* pg; double* lstar; PivCtl* ctl;
-  long* piv_g; long* piv_s; unsigned char* mark;
-  int* cslot; long* cand; double* R; double* R2; double* Ac; double* Lc; double* wc;
-  double* td[2]; long* tg[2];
-  int nparts, ldl;
+  double* d; double* L; PivPlan* plan; long* cand; double* R; double* R2; double* Ac; double* Lc;
+  double* wc; double* td; long* tg;
+  int n_lists, ldl;
 };
-
-static long top_entries(int64_t n_g) { return (long)cdiv(n_g, TOP_SEG) * NCAND; }
 
 static SelLayout layout_sel(Arena& ar, int64_t n_g, int n_orb, int n_mu) {
   SelLayout S;
-  S.nparts = (int)cdiv(n_g, PIV_BLOCK);
+  S.n_lists = (int)cdiv(n_g, TOP_PTS);
   S.ldl = n_mu > 0 ? n_mu : 1;
   S.d = ar.take<double>(n_g);
   S.L = ar.take<double>((size_t)n_mu * n_g);
-  S.pd = ar.take<double>(S.nparts);
-  S.pg = ar.take<long>(S.nparts);
-  S.lstar = ar.take<double>(NCAND);
-  S.ctl = ar.take<PivCtl>(1);
-  S.piv_g = ar.take<long>(n_mu + 1);
-  S.piv_s = ar.take<long>(n_mu + 1);
-  S.mark = ar.take<unsigned char>(n_g);
-  S.cslot = ar.take<int>(n_g);
+  S.plan = ar.take<PivPlan>(1);
   S.cand = ar.take<long>(NCAND);
   S.R = ar.take<double>((size_t)NCAND * n_g);
   S.R2 = ar.take<double>((size_t)NCAND * n_g);
   S.Ac = ar.take<double>((size_t)NCAND * 4 * n_orb);
   S.Lc = ar.take<double>((size_t)NCAND * S.ldl);
   S.wc = ar.take<double>(NCAND);
-  for (int b = 0; b < 2; ++b) {
-    S.td[b] = ar.take<double>(top_entries(n_g));
-    S.tg[b] = ar.take<long>(top_entries(n_g));
-  }
+  S.td = ar.take<double>((size_t)S.n_lists * NCAND);
+  S.tg = ar.take<long>((size_t)S.n_lists * NCAND);
   return S;
 }
 
@@ -394,27 +443,17 @@ static bool progress_enabled() {
   return on;
 }
 
-// Opens a batch at the current d: candidate search, stamps, and the candidates'
-// columns R against every point (GEMMs on the orbitals and the mu0 factor rows).
+// Opens a batch: the previous batch's n_acc accepted rows (before mu0) taken off d, the
+// candidate search, and the candidates' columns R against every point (GEMMs on the
+// orbitals and the mu0 factor rows).
 static xtc_status open_batch(const double* phi4, const double* w, long n_g, int n_orb,
-                             int channel, int mu0, int stamp, SelLayout& S, hipStream_t st) {
-  // candidate search
-  long n_in = n_g;
-  const double* id = S.d;
-  const long* ig = nullptr;
-  int b = 0;
-  for (;;) {
-    const unsigned nb = cdiv(n_in, TOP_SEG);
-    hipLaunchKernelGGL(k_top_sort, dim3(nb), dim3(256), 0, st, id, ig, n_in, S.td[b], S.tg[b]);
-    XTC_CHECK_LAUNCH();
-    id = S.td[b];
-    ig = S.tg[b];
-    n_in = (long)nb * NCAND;
-    b ^= 1;
-    if (nb == 1) break;
-  }
-  hipLaunchKernelGGL(k_batch_begin, dim3(1), dim3(NCAND), 0, st, id, ig, n_g, S.cslot, stamp,
-                     S.cand, S.ctl);
+                             int channel, int mu0, int n_acc, SelLayout& S, hipStream_t st) {
+  hipLaunchKernelGGL(k_top_local, dim3(S.n_lists), dim3(256), 0, st, S.d, n_g,
+                     (const double*)S.L, (long)(mu0 - n_acc), n_acc, (const PivPlan*)S.plan, S.td,
+                     S.tg);
+  XTC_CHECK_LAUNCH();
+  hipLaunchKernelGGL(k_top_merge, dim3(1), dim3(1024), 0, st, (const double*)S.td,
+                     (const long*)S.tg, S.n_lists, n_g, S.cand);
   XTC_CHECK_LAUNCH();
   const int nrows = channel == 0 ? n_orb : 4 * n_orb;
   hipLaunchKernelGGL(k_gather_cand, dim3(cdiv((long)NCAND * (nrows + mu0), 256)), dim3(256), 0, st,
@@ -452,58 +491,63 @@ static xtc_status open_batch(const double* phi4, const double* w, long n_g, int 
   return XTC_OK;
 }
 
-// Runs one channel; returns the number of pivots recorded.
+// Runs one channel: its pivots to `piv` in order, at most max_steps. target > 0: stops after
+// the pivot with which the union with `mark` (an entry per grid point, updated) holds target
+// points. *deficient: the channel ended at the rank tolerance.
 static xtc_status run_channel(const double* phi4, const double* w, long n_g, int n_orb, int channel,
-                              int max_steps, SelLayout& S, long* piv_out, hipStream_t st,
-                              int* n_out, int* deficient) {
-  const unsigned nb = (unsigned)S.nparts;
-  hipLaunchKernelGGL(k_diag, dim3(nb), dim3(PIV_BLOCK), 0, st, phi4, w, n_g, n_orb, channel, S.d,
-                     S.pd, S.pg);
+                              int max_steps, SelLayout& S, std::vector<char>& mark, int target,
+                              std::vector<long>& piv, hipStream_t st, int* deficient) {
+  hipLaunchKernelGGL(k_diag, dim3(cdiv(n_g, PIV_BLOCK)), dim3(PIV_BLOCK), 0, st, phi4, w, n_g,
+                     n_orb, channel, S.d);
   XTC_CHECK_LAUNCH();
-  XTC_HIP(hipMemsetAsync(S.cslot, 0, sizeof(int) * (size_t)n_g, st));
-  const int mode = channel == 0 ? 1 : 0;
-  PivCtl h{};
-  int done = 0, stamp = 0, guess = 16;
-  while (done < max_steps) {
-    ++stamp;
-    XTC_TRY(open_batch(phi4, w, n_g, n_orb, channel, done, stamp, S, st));
-    // steps are issued in groups, with a look at the control word after each: the
-    // first group is sized from the previous batch's length
-    const int lim = max_steps - done < NCAND ? max_steps - done : NCAND;
-    int issued = 0;
-    for (;;) {
-      int n = issued == 0 ? guess : 8;
-      if (n > lim - issued) n = lim - issued;
-      for (int i = 0; i < n; ++i) {
-        const int first = done == 0 && issued == 0 && i == 0;
-        hipLaunchKernelGGL(k_pick, dim3(1), dim3(PIV_BLOCK), 0, st, S.pd, S.pg, S.nparts, S.ctl,
-                           piv_out, S.L, n_g, S.lstar, S.mark, S.cslot, mode, first);
-        hipLaunchKernelGGL(k_column, dim3(nb), dim3(PIV_BLOCK), 0, st, S.R, n_g, S.L, S.lstar,
-                           S.ctl, S.d, S.pd, S.pg);
+  PivPlan h;
+  int done = 0, n_acc = 0, batches = 0, stop = 0, guess = NPLAN;
+  int in_union = 0;
+  for (char m : mark) in_union += m;
+  double d0max = 0.0;
+  while (done < max_steps && !stop) {
+    ++batches;
+    XTC_TRY(open_batch(phi4, w, n_g, n_orb, channel, done, n_acc, S, st));
+    // steps past the last accepted one are made for nothing: plan a few more than the
+    // previous batch accepted
+    const int lim = max_steps - done < guess ? max_steps - done : guess;
+    hipLaunchKernelGGL(k_plan, dim3(1), dim3(256), 0, st, (const double*)S.R, (const double*)S.d,
+                       n_g, (const long*)S.cand, lim, d0max, S.plan);
+    XTC_CHECK_LAUNCH();
+    hipLaunchKernelGGL(k_replay, dim3(cdiv(n_g, PIV_BLOCK)), dim3(PIV_BLOCK), 0, st,
+                       (const double*)S.R, n_g, (const double*)S.d, S.L, (long)done, S.plan,
+                       (const PivPlan*)S.plan);
+    XTC_CHECK_LAUNCH();
+    XTC_HIP(hipMemcpyAsync(&h, S.plan, offsetof(PivPlan, lstar), hipMemcpyDeviceToHost, st));
+    XTC_HIP(hipStreamSynchronize(st));
+    n_acc = 0;
+    while (n_acc < h.steps && !h.mark[n_acc] && !stop) {
+      const long g = h.g[n_acc++];
+      XTC_REQUIRE(g >= 0 && g < n_g, "isdf_select_points: the pivot search left the grid "
+                                     "(non-finite orbital values or weights?)");
+      piv.push_back(g);
+      if (!mark[g]) {
+        mark[g] = 1;
+        ++in_union;
       }
-      XTC_CHECK_LAUNCH();
-      issued += n;
-      XTC_HIP(hipMemcpyAsync(&h, S.ctl, sizeof(PivCtl), hipMemcpyDeviceToHost, st));
-      XTC_HIP(hipStreamSynchronize(st));
-      if (h.stop || h.bend || issued >= lim) break;
+      if (target > 0 && in_union >= target) stop = 2;   // the completing pivot is recorded
     }
-    const int accepted = h.step - done;
+    if (!stop && h.stop && n_acc == h.steps && !h.mark[h.steps]) stop = 1;
     // the batch's first pick is the largest d, its first candidate: no progress and no
-    // stop means the search and the argmax disagree, which only non-finite values cause
-    if (accepted == 0 && h.stop == 0) {
+    // stop means the search and the plan disagree, which only non-finite values cause
+    if (n_acc == 0 && !stop) {
       set_error("isdf_select_points: the pivot search made no progress (non-finite orbital "
                 "values or weights?)");
       return XTC_ERR_INVALID_ARG;
     }
-    guess = accepted + 4 < NCAND ? accepted + 4 : NCAND;
-    if (progress_enabled() && h.step / 1024 != done / 1024)
+    if (d0max <= 0.0) d0max = h.d[0];
+    guess = n_acc + 12 < NPLAN ? n_acc + 12 : NPLAN;
+    if (progress_enabled() && (done + n_acc) / 1024 != done / 1024)
       fprintf(stderr, "isdf_select_points: %s channel, %d steps done (%d batches)\n",
-              channel == 0 ? "scalar" : "gradient", h.step, stamp);
-    done = h.step;
-    if (h.stop != 0) break;
+              channel == 0 ? "scalar" : "gradient", done + n_acc, batches);
+    done += n_acc;
   }
-  *n_out = done;
-  *deficient = (h.stop == 1);
+  *deficient = stop == 1;
   return XTC_OK;
 }
 
@@ -526,26 +570,16 @@ xtc_status xtc_select_qr(const double* phi4, const xtc_grid* grid, int n_orb, in
   const size_t mark = ar.used;
   SelLayout S = layout_sel(ar, n_g, n_orb, n_mu);
   XTC_TRY(need_ws(ar));
-  XTC_HIP(hipMemsetAsync(S.mark, 0, n_g, st));
-  // gradient channel to ceil(n_mu / 2) pivots
-  const int n_grad = (n_mu + 1) / 2;
-  PivCtl init{};
-  init.target = 0;
-  XTC_HIP(hipMemcpyAsync(S.ctl, &init, sizeof(PivCtl), hipMemcpyHostToDevice, st));
-  int ng = 0, defg = 0;
-  XTC_TRY(run_channel(phi4, grid->w, n_g, n_orb, 1, n_grad, S, S.piv_g, st, &ng, &defg));
-  // scalar channel until the union reaches n_mu
-  init.union_n = ng;
-  init.target = n_mu;
-  XTC_HIP(hipMemcpyAsync(S.ctl, &init, sizeof(PivCtl), hipMemcpyHostToDevice, st));
-  int ns = 0, defs = 0;
-  if (ng < n_mu) {
-    XTC_TRY(run_channel(phi4, grid->w, n_g, n_orb, 0, n_mu, S, S.piv_s, st, &ns, &defs));
-  }
-  std::vector<long> hg(ng > 0 ? ng : 1), hs(ns > 0 ? ns : 1);
-  if (ng) XTC_HIP(hipMemcpyAsync(hg.data(), S.piv_g, sizeof(long) * ng, hipMemcpyDeviceToHost, st));
-  if (ns) XTC_HIP(hipMemcpyAsync(hs.data(), S.piv_s, sizeof(long) * ns, hipMemcpyDeviceToHost, st));
-  XTC_HIP(hipStreamSynchronize(st));
+  // gradient channel to ceil(n_mu / 2) pivots, then the scalar channel until the union
+  // reaches n_mu
+  std::vector<char> in_union(n_g, 0);
+  std::vector<long> hg, hs;
+  int defg = 0, defs = 0;
+  XTC_TRY(run_channel(phi4, grid->w, n_g, n_orb, 1, (n_mu + 1) / 2, S, in_union, 0, hg, st, &defg));
+  const int ng = (int)hg.size();
+  if (ng < n_mu)
+    XTC_TRY(run_channel(phi4, grid->w, n_g, n_orb, 0, n_mu, S, in_union, n_mu, hs, st, &defs));
+  const int ns = (int)hs.size();
   // fused order: scalar pivots in selection order, then gradient-only pivots
   std::vector<char> in_s(n_g, 0);
   int n = 0;
