@@ -17,7 +17,7 @@
 // Workgroup 256 threads = 4 waves over a 128 x 128 tile of C; wave (wm, wn) owns
 // the 64 x 64 sub-tile = 2 x 2 MFMA blocks. The k-step ahead is loaded while the
 // current one is multiplied; scheduling fences keep those loads in place.
-#include "common.hpp"
+#include "half_round.hpp"
 #include "gemm_split.hpp"
 #include "timing.hpp"
 
@@ -146,9 +146,8 @@ __global__ __launch_bounds__(256) void k_split_tiles(SegOperand o, long rows,
     double v = 0.0;
     if (r < rows && sg < o.nseg && k < o.K) v = seg_value(o, sg, r, k);
     v *= sc;
-    const _Float16 h = (_Float16)(float)v;
-    hi[q] = h;
-    lo[q] = (_Float16)(float)(v - (double)(float)h);
+    hi[q] = half_of(v);
+    lo[q] = half_of(v - (double)(float)hi[q]);
   }
   const long base = ((rb * nks + ks) * 2) * 64 + lane;
   T[base] = hi;
@@ -220,9 +219,8 @@ __global__ __launch_bounds__(256) void k_split_tiles_k1(SegOperand o, long rows,
 #pragma unroll
   for (int q = 0; q < 8; ++q) {
     const double x = v[q] * sc;
-    const _Float16 h = (_Float16)(float)x;
-    hi[q] = h;
-    lo[q] = (_Float16)(float)(x - (double)(float)h);
+    hi[q] = half_of(x);
+    lo[q] = half_of(x - (double)(float)hi[q]);
   }
   const long base = ((rb * nks + ks) * 2) * 64 + lane;
   T[base] = hi;

@@ -24,6 +24,7 @@
 //   A[l % 32][8 (l / 32) + e]   B[8 (l / 32) + e][l % 32]
 //   D[8 (r / 4) + 4 (l / 32) + r % 4][l % 32]
 #include <type_traits>
+#include "half_round.hpp"
 #include "stage1_split.hpp"
 #include "timing.hpp"
 
@@ -107,10 +108,8 @@ __global__ __launch_bounds__(256) void k_split_A(const double* __restrict__ w,
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
     const double v = a_value(w, xi, n_g, n_mu, row, k0 + e) * sc;
-    const float vf = (float)v;
-    const _Float16 h = (_Float16)vf;
-    hi[e] = h;
-    lo[e] = (_Float16)((float)(v - (double)(float)h));
+    hi[e] = half_of(v);
+    lo[e] = half_of(v - (double)(float)hi[e]);
   }
   const long base = ((rb * nks + ks) * 2) * 64 + lane;
   At[base] = hi;
