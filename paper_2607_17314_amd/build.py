@@ -40,7 +40,6 @@ FLAGS = [
 FILE_FLAGS = {
     "gemm_f64.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
     "grad.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
-    "bh_pairs.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
     "stage1_products.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
 }
 

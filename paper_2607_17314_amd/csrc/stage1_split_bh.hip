@@ -5,22 +5,21 @@
 // operations per pair). The BH values cost ~40 FP64 operations per nucleus and pair (the
 // nuclear sums F_o and grad F_o), which beside the MFMAs of one 256-row tile would be made
 // again for every row tile. Here they are made once per pair and launch:
-//   1. k_bh_pairs (bh_pairs.hip): the four channels of every (bra, ket) pair of a bra
-//      tile and a ket chunk in FP64, scaled by a power of two and split into FP16 (hi, lo),
-//      stored in the MFMA B-fragment order of the split pair kernel; the same FP64 values
-//      feed the two density rows (rows n_mu and n_mu + 1), summed in FP64 per bra point;
+//   1. k_bh_pairs (vector FP64): the four channels of every (bra, ket) pair of a bra
+//      tile and a ket chunk, scaled by a power of two and split into FP16 (hi, lo), stored
+//      in the MFMA B-fragment order of the split pair kernel; the same FP64 values feed
+//      the two density rows (rows n_mu and n_mu + 1), summed in FP64 per bra point;
 //   2. k_stage1_split_pv: the split products A_hi K_hi + A_hi K_lo + A_lo K_hi with
 //      v_mfma_f32_32x32x16_f16, the pair values streamed from the buffer through LDS
 //      (double-buffered, one ket chunk ahead), FP32 accumulation over a pair of chunks,
 //      an FP32 medium sum over the launch, FP64 in the panel, scales removed exactly.
 // The A operand and its per-row exponents are the split operand of the EE path. The FP64
-// path of the BH form takes its pair values from k_bh_pairs_f64 below (nuclear sums on the
-// vector units, the values stored unscaled in FP64 for the products of stage1_products.hip).
+// path of the BH form takes its pair values from k_bh_pairs_f64 below (the same tables and
+// sums, the values stored unscaled in FP64 for k_stage1_f64_pv).
 #include <algorithm>
 #include <type_traits>
 #include "bh.hpp"
 #include "stage1_split.hpp"
-#include "stage1_split_bh.hpp"
 #include "timing.hpp"
 
 namespace xtc {
@@ -29,6 +28,9 @@ namespace xtc {
 // not relied on to order them with other waves' reads that follow it.
 #define XTC_LDS_DONE() __builtin_amdgcn_s_waitcnt(0xc07f)
 #define XTC_FENCE() __builtin_amdgcn_sched_barrier(0)
+
+constexpr int GCH = 8;                // ket chunks per generation workgroup
+constexpr int PV_CHUNK = 8 * 4 * 2 * 64;   // h8 per (bra tile, ket chunk): [ks][ch][hl][lane]
 
 size_t bh_split_scratch_bytes(long bp) {
   return (size_t)cdiv(bp, SB) * SMED * PV_CHUNK * sizeof(h8) + 256;
@@ -88,11 +90,17 @@ __device__ __forceinline__ void ket_gamma_lds(const double (*NU)[4], const int* 
 // (4 banks) apart modulo the 64 banks, instead of all in one bank.
 __host__ __device__ constexpr int bh_ket_stride(int nn) { return nn * BH_NO * BH_NP + 2; }
 
-// LDS tables of k_bh_pairs_f64, in doubles: bra tables [nn][a, grad a][32 bras],
+// LDS tables of the pair-value kernels, in doubles: bra tables [nn][a, grad a][32 bras],
 // ket tables [16 kets][bh_ket_stride(nn)], csym [t][m][n][o], nuclei [BH_MAXNUC][x, y, z, b]
 __host__ __device__ constexpr long bh_tables_lds_doubles(int nn) {
   return (long)nn * 4 * SB + 16L * bh_ket_stride(nn) + BH_MAXTYPE * BH_NP * BH_NP * BH_NO +
          4L * BH_MAXNUC;
+}
+
+// LDS of k_bh_pairs: the tables, then the staged half-precision fragments (two k-steps'
+// worth, 2 x 4096 halves)
+__host__ __device__ constexpr long bh_pairs_lds_doubles(int nn) {
+  return bh_tables_lds_doubles(nn) + 2 * 4096 / 4;
 }
 
 struct BHLds {
@@ -173,8 +181,121 @@ __device__ __forceinline__ void bh_two_pairs(const BHLds& L, int nn, int q2, int
   }
 }
 
-// The FP64 path's pair values (the BH form): per thread two pairs walking the nuclei over LDS
-// tables, the four channels stored unscaled in FP64 for k_stage1_products, per 16-ket step s of the
+// One workgroup: bra tile blockIdx.x (32 points) x the GCH ket chunks of group blockIdx.y
+// of the launch. Per k-step (16 kets) the ket tables gamma_{I,o,m} go to LDS, then thread
+// (ket kk = tid % 16, bra pair q = tid / 16) makes the pairs (bra 2 q + v, ket kk), v = 0, 1:
+// each ket table read from LDS serves two pairs. The split values are staged in LDS in the
+// B-fragment order (slot L = bra + 32 (kk / 8), element kk % 8) and copied out, 16 bytes per
+// lane, during the next k-step. The density-row sums of each bra are added over the
+// workgroup in a fixed order and written (first launch) or added (later launches) to
+// part[group][8][bp].
+__global__ __launch_bounds__(256) void k_bh_pairs(
+    const double* __restrict__ xyz, const double* __restrict__ w, const double* __restrict__ rho,
+    const double* __restrict__ rhot, long n_g, long b0, long bn, long c0, long nloc, EECoef cf,
+    const BHTable* __restrict__ T, int eg, int es, h8* __restrict__ pv,
+    double* __restrict__ part, long bp, int first) {
+  extern __shared__ double sm[];
+  const int nn = T->n_nuc;
+  const BHLds L = bh_lds(sm, nn);
+  h8* ST = (h8*)(sm + bh_tables_lds_doubles(nn));   // [2][512] h8
+  _Float16* STh = (_Float16*)ST;
+  const int tid = threadIdx.x, kk = tid & 15, q2 = tid >> 4;
+  const long bt = blockIdx.x;
+  const long blast = b0 + bn - 1;
+  bh_fill_bra_tables(L, T, xyz, n_g, b0, bn, bt, nn, tid);
+  double xb[2], yb[2], zb[2];
+#pragma unroll
+  for (int v = 0; v < 2; ++v) {
+    long b = b0 + bt * SB + 2 * q2 + v;
+    if (b > blast) b = blast;
+    xb[v] = xyz[b];
+    yb[v] = xyz[n_g + b];
+    zb[v] = xyz[2 * n_g + b];
+  }
+  const double sg = ldexp(1.0, eg), ss = ldexp(1.0, es);
+  double s[2][4] = {}, h[2][4] = {};
+  const long cl0 = (long)blockIdx.y * GCH;
+  const long cl1 = cl0 + GCH < nloc ? cl0 + GCH : nloc;
+  long prev = -1;   // pv index of the staged k-step's first fragment
+  for (long cl = cl0; cl < cl1; ++cl) {
+    for (int j = 0; j < 8; ++j) {
+      const long k0 = (c0 + cl) * SKC + 16 * j;
+      __syncthreads();   // TK free again; the previous k-step's staging complete
+      if (prev >= 0) {
+        const h8* src = ST + ((j + 7) & 1) * 512;   // the buffer of the previous k-step
+        pv[prev + tid] = src[tid];
+        pv[prev + 256 + tid] = src[256 + tid];
+      }
+      bh_fill_ket_tables(L, T, xyz, n_g, k0, nn, tid);
+      __syncthreads();
+      const long g = k0 + kk;
+      const long gc = g < n_g ? g : n_g - 1;   // padding kets: finite values, zero weight
+      const double kx = xyz[gc], ky = xyz[n_g + gc], kz = xyz[2 * n_g + gc];
+      const double a = g < n_g ? w[g] * rho[g] : 0.0, at = g < n_g ? w[g] * rhot[g] : 0.0;
+      unsigned pk[2][4];   // per bra and channel: (hi, lo) halves of the scaled value
+      double F[2][BH_NO], GF[2][BH_NO][3];
+      bh_two_pairs(L, nn, q2, kk, F, GF);
+#pragma unroll
+      for (int v = 0; v < 2; ++v) {
+        double o[4];
+        bh_finish(cf, F[v], GF[v], xb[v] - kx, yb[v] - ky, zb[v] - kz, o);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          s[v][c] = fma(a, o[c], s[v][c]);
+          h[v][c] = fma(at, o[c], h[v][c]);
+          const double x = o[c] * (c < 3 ? sg : ss);
+          const _Float16 hi = (_Float16)(float)x;
+          const _Float16 lo = (_Float16)(float)(x - (double)hi);
+          pk[v][c] = (unsigned)__builtin_bit_cast(unsigned short, hi) |
+                     ((unsigned)__builtin_bit_cast(unsigned short, lo) << 16);
+        }
+      }
+      // lanes kk = 2p and 2p + 1 (adjacent lanes) trade values so that each writes whole
+      // 32-bit words: the even lane elements (2p, 2p + 1) of bra 2 q, the odd lane those of
+      // bra 2 q + 1
+      const bool odd = kk & 1;
+      unsigned* dw = (unsigned*)(STh + (j & 1) * 4096);
+      const int bw = 2 * q2 + (odd ? 1 : 0);
+      const int slot = bw + 32 * (kk >> 3);
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        const unsigned mine = odd ? pk[1][c] : pk[0][c];
+        const unsigned other = (unsigned)__shfl_xor((int)(odd ? pk[0][c] : pk[1][c]), 1);
+        const unsigned e0 = odd ? other : mine, e1 = odd ? mine : other;   // kets 2p, 2p + 1
+        dw[(((c * 2 + 0) * 64 + slot) * 8 + (kk & 6)) / 2] = (e0 & 0xffffu) | (e1 << 16);
+        dw[(((c * 2 + 1) * 64 + slot) * 8 + (kk & 6)) / 2] = (e0 >> 16) | (e1 & 0xffff0000u);
+      }
+      XTC_LDS_DONE();
+      prev = (bt * nloc + cl) * PV_CHUNK + j * 512;
+    }
+  }
+  __syncthreads();
+  pv[prev + tid] = ST[512 + tid];   // the last k-step (j = 7) staged in buffer 1
+  pv[prev + 256 + tid] = ST[512 + 256 + tid];
+  __syncthreads();
+  double* red = sm;   // [8 sums][32 bras][16 kets], over the tables and the staging
+#pragma unroll
+  for (int v = 0; v < 2; ++v)
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      red[(c * SB + 2 * q2 + v) * 16 + kk] = s[v][c];
+      red[((4 + c) * SB + 2 * q2 + v) * 16 + kk] = h[v][c];
+    }
+  XTC_LDS_DONE();
+  __syncthreads();
+  const int qq = tid >> 5, bb = tid & 31;
+  double v = 0.0;
+#pragma unroll
+  for (int c = 0; c < 16; ++c) v += red[(qq * SB + bb) * 16 + c];
+  const long tb = bt * SB + bb;
+  if (tb < bn) {
+    double* p = part + ((long)blockIdx.y * 8 + qq) * bp + tb;
+    *p = first ? v : *p + v;
+  }
+}
+
+// The FP64 path's pair values (the BH form): the same tables and nuclear sums as k_bh_pairs,
+// the four channels stored unscaled in FP64 for k_stage1_f64_pv, per 16-ket step s of the
 // launch and 64-bra tile t: pv64[t][s][q][c][gk][gb] for the pair (bra gb, ket 4 gk + q).
 // The grid covers whole 64-bra tiles (two 32-bra halves; bras past the range repeat its
 // last point).
@@ -423,6 +544,8 @@ xtc_status stage1_split_bh(const Stage1Args& a, const EECoef& cf, void* scratch,
   h8* pv = (h8*)((char*)scratch + off_pv);
   int eg = 0, es = 0;
   bh_split_exponents(*a.bh_host, cf, &eg, &es);
+  const int nn = a.bh_host->n_nuc;
+  const size_t lds_gen = sizeof(double) * (size_t)std::max(bh_pairs_lds_doubles(nn), 8L * SB * 16);
   const size_t lds_pv = sizeof(h8) * 2 * PV_CHUNK;
   const int nrt = (int)(S.rows_pad / SR);
   const long nchunks = S.n_g_pad / SKC;
@@ -435,7 +558,9 @@ xtc_status stage1_split_bh(const Stage1Args& a, const EECoef& cf, void* scratch,
   for (long c0 = 0; c0 < nchunks; c0 += SMED) {
     const long nloc = SMED < nchunks - c0 ? SMED : nchunks - c0;
     size_t tk = timing_begin(TM_S1_PAIRS, st);
-    XTC_TRY(bh_pair_values_split(a, cf, c0, nloc, eg, es, pv, part, c0 == 0 ? 1 : 0, st));
+    hipLaunchKernelGGL(k_bh_pairs, dim3(nbt, cdiv(nloc, GCH)), dim3(256), lds_gen, st, a.xyz, a.w,
+                       a.rho, a.rhot, a.n_g, a.b0, a.bn, c0, nloc, cf, a.bh, eg, es, pv, part,
+                       a.bp, c0 == 0 ? 1 : 0);
     timing_end(tk, st);
     XTC_CHECK_LAUNCH();
     tk = timing_begin(TM_S1_KERNEL, st);
