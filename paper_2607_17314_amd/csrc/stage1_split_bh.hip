@@ -19,6 +19,7 @@
 #include <algorithm>
 #include <type_traits>
 #include "bh.hpp"
+#include "half_round.hpp"
 #include "stage1_split.hpp"
 #include "timing.hpp"
 
@@ -65,36 +66,16 @@ static void bh_split_exponents(const BHTable& T, const EECoef& cf, int* eg, int*
   *es = 14 - 2 * ex;
 }
 
-// gamma_{I,o,m} of one ket point (see bh.hpp) from the workgroup's LDS copies of the
-// nuclei (x, y, z, b) and of csym
-__device__ __forceinline__ void ket_gamma_lds(const double (*NU)[4], const int* __restrict__ ty,
-                                              const double* CS, int I, double x, double y,
-                                              double z, double* out) {
-  const double dx = x - NU[I][0], dy = y - NU[I][1], dz = z - NU[I][2];
-  const double r = sqrt(dx * dx + dy * dy + dz * dz);
-  const double a = NU[I][3] * r / (1.0 + NU[I][3] * r);
-  const double A2[BH_NP] = {1.0, a, a * a, a * a * a};
-  const double* c = CS + ty[I] * (BH_NP * BH_NP * BH_NO);   // [m][n][o]
-#pragma unroll
-  for (int o = 0; o < BH_NO; ++o)
-#pragma unroll
-    for (int m = 0; m < BH_NP; ++m) {
-      double v = 0.0;
-#pragma unroll
-      for (int n = 0; n < BH_NP; ++n) v += c[(m * BH_NP + n) * BH_NO + o] * A2[n];
-      out[o * BH_NP + m] = v;
-    }
-}
-
 // Doubles per ket in the LDS ket tables: the 16 kets of a wave read at once sit 2 doubles
 // (4 banks) apart modulo the 64 banks, instead of all in one bank.
 __host__ __device__ constexpr int bh_ket_stride(int nn) { return nn * BH_NO * BH_NP + 2; }
 
-// LDS tables of the pair-value kernels, in doubles: bra tables [nn][a, grad a][32 bras],
-// ket tables [16 kets][bh_ket_stride(nn)], csym [t][m][n][o], nuclei [BH_MAXNUC][x, y, z, b]
+// LDS tables of the pair-value kernels, in doubles: bra tables [nn][a, grad a][32 bras], two
+// ket tables [16 kets][bh_ket_stride(nn)], two tables a_I [nn][16 kets], csym [t][m][n][o],
+// nuclei [BH_MAXNUC][x, y, z, b]
 __host__ __device__ constexpr long bh_tables_lds_doubles(int nn) {
-  return (long)nn * 4 * SB + 16L * bh_ket_stride(nn) + BH_MAXTYPE * BH_NP * BH_NP * BH_NO +
-         4L * BH_MAXNUC;
+  return (long)nn * 4 * SB + 2 * 16L * bh_ket_stride(nn) + 2 * 16L * nn +
+         BH_MAXTYPE * BH_NP * BH_NP * BH_NO + 4L * BH_MAXNUC;
 }
 
 // LDS of k_bh_pairs: the tables, then the staged half-precision fragments (two k-steps'
@@ -105,7 +86,8 @@ __host__ __device__ constexpr long bh_pairs_lds_doubles(int nn) {
 
 struct BHLds {
   double (*TB)[4][SB];   // bra tables of the 32-bra tile
-  double* TK;            // ket tables of the current 16-ket step
+  double* TK;            // ket tables of 16-ket steps, even, then odd
+  double* AT;            // their a_I
   double* CS;            // csym
   double (*NU)[4];       // nuclei
   int ks;                // doubles per ket in TK
@@ -116,7 +98,8 @@ __device__ __forceinline__ BHLds bh_lds(double* sm, int nn) {
   L.TB = (double(*)[4][SB])sm;
   L.ks = bh_ket_stride(nn);
   L.TK = sm + nn * 4 * SB;
-  L.CS = L.TK + 16 * L.ks;
+  L.AT = L.TK + 2 * 16 * L.ks;
+  L.CS = L.AT + 2 * 16 * nn;
   L.NU = (double(*)[4])(L.CS + BH_MAXTYPE * BH_NP * BH_NP * BH_NO);
   return L;
 }
@@ -142,25 +125,84 @@ __device__ __forceinline__ void bh_fill_bra_tables(const BHLds& L, const BHTable
   XTC_LDS_DONE();
 }
 
-// the ket tables of kets k0 .. k0 + 15 (kets past the grid repeat its last point); between
-// barriers
-__device__ __forceinline__ void bh_fill_ket_tables(const BHLds& L, const BHTable* __restrict__ T,
-                                                   const double* __restrict__ xyz, long n_g,
-                                                   long k0, int nn, int tid) {
-  for (int e = tid; e < 16 * nn; e += 256) {
-    long g = k0 + e / nn;
+// a_I of ket tid % 16 of a step at (x, y, z), nuclei tid / 16, tid / 16 + 16
+__device__ __forceinline__ void bh_ket_a(const BHLds& L, double* AT, double x, double y, double z,
+                                         int nn, int tid) {
+  for (int I = tid >> 4; I < nn; I += 16) {
+    const double dx = x - L.NU[I][0], dy = y - L.NU[I][1], dz = z - L.NU[I][2];
+    const double r = sqrt(dx * dx + dy * dy + dz * dz);
+    AT[I * 16 + (tid & 15)] = L.NU[I][3] * r / (1.0 + L.NU[I][3] * r);
+  }
+}
+
+// gamma_{I,o,m} (bh.hpp) of ket tid % 16 and (o, m) = tid / 16, all nuclei, from the a_I;
+// types: bit I is the type of nucleus I
+__device__ __forceinline__ void bh_ket_gamma(const BHLds& L, const double* AT, double* TK, int nn,
+                                             unsigned types, int tid) {
+  const int kk = tid & 15, om = tid >> 4;
+  const double* cs = L.CS + (om % BH_NP) * BH_NP * BH_NO + om / BH_NP;   // [n] at stride BH_NO
+  double c[BH_MAXTYPE][BH_NP];
+#pragma unroll
+  for (int t = 0; t < BH_MAXTYPE; ++t)
+#pragma unroll
+    for (int n = 0; n < BH_NP; ++n) c[t][n] = cs[t * BH_NP * BH_NP * BH_NO + n * BH_NO];
+#pragma unroll 2
+  for (int I = 0; I < nn; ++I) {
+    const bool t1 = (types >> I) & 1;
+    const double a = AT[I * 16 + kk];
+    const double A2[BH_NP] = {1.0, a, a * a, a * a * a};
+    double v = 0.0;
+#pragma unroll
+    for (int n = 0; n < BH_NP; ++n) v += (t1 ? c[1][n] : c[0][n]) * A2[n];
+    TK[kk * L.ks + I * BH_NO * BH_NP + om] = v;
+  }
+}
+
+// The 16-ket steps of a workgroup from ket kbeg (kets past the grid repeat its last point):
+// pairs(step) with its ket tables in half step & 1 of L.TK. While a step's pairs are made, the
+// gammas of the next step and the a_I of the one after it go to the other tables, so that a
+// step has one barrier and nothing to wait for behind it. top(step) comes first in a step,
+// for loads and for stores of what the step before left in LDS.
+template <class Top, class Pairs>
+__device__ __forceinline__ void bh_ket_steps(const BHLds& L, const BHTable* __restrict__ T,
+                                             const double* __restrict__ xyz, long n_g, long kbeg,
+                                             int nsteps, int nn, int tid, Top top, Pairs pairs) {
+  unsigned types = 0;
+  for (int I = 0; I < nn; ++I) types |= (unsigned)T->type[I] << I;
+  auto ket = [&](int s, double& x, double& y, double& z) {
+    long g = kbeg + 16L * s + (tid & 15);
     if (g > n_g - 1) g = n_g - 1;
-    ket_gamma_lds(L.NU, T->type, L.CS, e % nn, xyz[g], xyz[n_g + g], xyz[2 * n_g + g],
-                  L.TK + (e / nn) * L.ks + (e % nn) * BH_NO * BH_NP);
+    x = xyz[g];
+    y = xyz[n_g + g];
+    z = xyz[2 * n_g + g];
+  };
+  double x, y, z;
+  __syncthreads();   // the nuclei, csym and bra tables are in
+  for (int i = 0; i < 2; ++i) {
+    ket(i, x, y, z);
+    bh_ket_a(L, L.AT + i * 16 * nn, x, y, z, nn, tid);
   }
   XTC_LDS_DONE();
+  __syncthreads();
+  bh_ket_gamma(L, L.AT, L.TK, nn, types, tid);
+  for (int s = 0; s < nsteps; ++s) {
+    XTC_LDS_DONE();
+    __syncthreads();
+    ket(s + 2, x, y, z);
+    top(s);
+    bh_ket_gamma(L, L.AT + ((s + 1) & 1) * 16 * nn, L.TK + ((s + 1) & 1) * 16 * L.ks, nn, types, tid);
+    pairs(s);
+    bh_ket_a(L, L.AT + (s & 1) * 16 * nn, x, y, z, nn, tid);
+  }
+  XTC_LDS_DONE();
+  __syncthreads();
 }
 
 // the nuclear sums of the pairs (bra 2 q2 + v, ket kk), v = 0, 1, in one pass over the
 // nuclei: each ket-table entry is read from LDS once for the two bras
-__device__ __forceinline__ void bh_two_pairs(const BHLds& L, int nn, int q2, int kk,
+__device__ __forceinline__ void bh_two_pairs(const BHLds& L, const double* TK, int nn, int q2, int kk,
                                              double (&F)[2][BH_NO], double (&GF)[2][BH_NO][3]) {
-  const double(*tk)[BH_NO][BH_NP] = (const double(*)[BH_NO][BH_NP])(L.TK + kk * L.ks);
+  const double(*tk)[BH_NO][BH_NP] = (const double(*)[BH_NO][BH_NP])(TK + kk * L.ks);
 #pragma unroll
   for (int v = 0; v < 2; ++v)
 #pragma unroll
@@ -182,14 +224,20 @@ __device__ __forceinline__ void bh_two_pairs(const BHLds& L, int nn, int q2, int
 }
 
 // One workgroup: bra tile blockIdx.x (32 points) x the GCH ket chunks of group blockIdx.y
-// of the launch. Per k-step (16 kets) the ket tables gamma_{I,o,m} go to LDS, then thread
-// (ket kk = tid % 16, bra pair q = tid / 16) makes the pairs (bra 2 q + v, ket kk), v = 0, 1:
-// each ket table read from LDS serves two pairs. The split values are staged in LDS in the
-// B-fragment order (slot L = bra + 32 (kk / 8), element kk % 8) and copied out, 16 bytes per
-// lane, during the next k-step. The density-row sums of each bra are added over the
-// workgroup in a fixed order and written (first launch) or added (later launches) to
-// part[group][8][bp].
-__global__ __launch_bounds__(256) void k_bh_pairs(
+// of the launch, in steps of 16 kets (bh_ket_steps). Thread (ket kk = tid % 16, bra pair
+// q = tid / 16) makes the pairs (bra 2 q + v, ket kk), v = 0, 1: each ket table entry read
+// from LDS serves two pairs. The split values are staged in LDS in the B-fragment order
+// (slot L = bra + 32 (kk / 8), element kk % 8) and copied out, 16 bytes per lane, during the
+// next step. The density-row sums of each bra are added over the workgroup in a fixed order
+// and written (first launch) or added (later launches) to part[group][8][bp].
+// Bound: vector issue, ~540 FP64 instructions a pair at ten nuclei (36 per nucleus, ~130 in
+// the square root, divisions and channels) and about half as many others. Ten nuclei, 58,200
+// points, mean of launches of up to 16,384 x 16,384 pairs: 9.09 ms with the ket tables filled
+// between two barriers of the step and the compiler's FP64 to FP16 conversion, 7.95 with
+// half_of, 6.95 with the tables made a step ahead. The sums as products over (nucleus, power)
+// on the matrix cores took 5.85 ms, but round otherwise in their last bits, and a few FP16
+// values in 10^10 then fall on their other side.
+__global__ __launch_bounds__(256, 2) void k_bh_pairs(
     const double* __restrict__ xyz, const double* __restrict__ w, const double* __restrict__ rho,
     const double* __restrict__ rhot, long n_g, long b0, long bn, long c0, long nloc, EECoef cf,
     const BHTable* __restrict__ T, int eg, int es, h8* __restrict__ pv,
@@ -216,62 +264,64 @@ __global__ __launch_bounds__(256) void k_bh_pairs(
   double s[2][4] = {}, h[2][4] = {};
   const long cl0 = (long)blockIdx.y * GCH;
   const long cl1 = cl0 + GCH < nloc ? cl0 + GCH : nloc;
-  long prev = -1;   // pv index of the staged k-step's first fragment
-  for (long cl = cl0; cl < cl1; ++cl) {
-    for (int j = 0; j < 8; ++j) {
-      const long k0 = (c0 + cl) * SKC + 16 * j;
-      __syncthreads();   // TK free again; the previous k-step's staging complete
-      if (prev >= 0) {
-        const h8* src = ST + ((j + 7) & 1) * 512;   // the buffer of the previous k-step
-        pv[prev + tid] = src[tid];
-        pv[prev + 256 + tid] = src[256 + tid];
-      }
-      bh_fill_ket_tables(L, T, xyz, n_g, k0, nn, tid);
-      __syncthreads();
-      const long g = k0 + kk;
-      const long gc = g < n_g ? g : n_g - 1;   // padding kets: finite values, zero weight
-      const double kx = xyz[gc], ky = xyz[n_g + gc], kz = xyz[2 * n_g + gc];
-      const double a = g < n_g ? w[g] * rho[g] : 0.0, at = g < n_g ? w[g] * rhot[g] : 0.0;
-      unsigned pk[2][4];   // per bra and channel: (hi, lo) halves of the scaled value
-      double F[2][BH_NO], GF[2][BH_NO][3];
-      bh_two_pairs(L, nn, q2, kk, F, GF);
+  const long kbeg = (c0 + cl0) * SKC;
+  h8* out = pv + (bt * nloc + cl0) * PV_CHUNK;   // step t's fragments at 512 t
+  double kx, ky, kz, a, at;
+  auto top = [&](int t) {
+    const long g = kbeg + 16L * t + kk;
+    const long gc = g < n_g ? g : n_g - 1;   // padding kets: finite values, zero weight
+    kx = xyz[gc];
+    ky = xyz[n_g + gc];
+    kz = xyz[2 * n_g + gc];
+    a = g < n_g ? w[g] * rho[g] : 0.0;
+    at = g < n_g ? w[g] * rhot[g] : 0.0;
+    if (t > 0) {
+      const h8* src = ST + ((t + 1) & 1) * 512;   // the buffer of the previous k-step
+      out[(t - 1) * 512 + tid] = src[tid];
+      out[(t - 1) * 512 + 256 + tid] = src[256 + tid];
+    }
+  };
+  auto pairs = [&](int t) {
+    unsigned pk[2][4];   // per bra and channel: (hi, lo) halves of the scaled value
+    double F[2][BH_NO], GF[2][BH_NO][3];
+    bh_two_pairs(L, L.TK + (t & 1) * 16 * L.ks, nn, q2, kk, F, GF);
 #pragma unroll
-      for (int v = 0; v < 2; ++v) {
-        double o[4];
-        bh_finish(cf, F[v], GF[v], xb[v] - kx, yb[v] - ky, zb[v] - kz, o);
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-          s[v][c] = fma(a, o[c], s[v][c]);
-          h[v][c] = fma(at, o[c], h[v][c]);
-          const double x = o[c] * (c < 3 ? sg : ss);
-          const _Float16 hi = (_Float16)(float)x;
-          const _Float16 lo = (_Float16)(float)(x - (double)hi);
-          pk[v][c] = (unsigned)__builtin_bit_cast(unsigned short, hi) |
-                     ((unsigned)__builtin_bit_cast(unsigned short, lo) << 16);
-        }
-      }
-      // lanes kk = 2p and 2p + 1 (adjacent lanes) trade values so that each writes whole
-      // 32-bit words: the even lane elements (2p, 2p + 1) of bra 2 q, the odd lane those of
-      // bra 2 q + 1
-      const bool odd = kk & 1;
-      unsigned* dw = (unsigned*)(STh + (j & 1) * 4096);
-      const int bw = 2 * q2 + (odd ? 1 : 0);
-      const int slot = bw + 32 * (kk >> 3);
+    for (int v = 0; v < 2; ++v) {
+      double o[4];
+      bh_finish(cf, F[v], GF[v], xb[v] - kx, yb[v] - ky, zb[v] - kz, o);
 #pragma unroll
       for (int c = 0; c < 4; ++c) {
-        const unsigned mine = odd ? pk[1][c] : pk[0][c];
-        const unsigned other = (unsigned)__shfl_xor((int)(odd ? pk[0][c] : pk[1][c]), 1);
-        const unsigned e0 = odd ? other : mine, e1 = odd ? mine : other;   // kets 2p, 2p + 1
-        dw[(((c * 2 + 0) * 64 + slot) * 8 + (kk & 6)) / 2] = (e0 & 0xffffu) | (e1 << 16);
-        dw[(((c * 2 + 1) * 64 + slot) * 8 + (kk & 6)) / 2] = (e0 >> 16) | (e1 & 0xffff0000u);
+        s[v][c] = fma(a, o[c], s[v][c]);
+        h[v][c] = fma(at, o[c], h[v][c]);
+        const double x = o[c] * (c < 3 ? sg : ss);
+        const _Float16 hi = half_of(x), lo = half_of(x - (double)(float)hi);
+        pk[v][c] = (unsigned)__builtin_bit_cast(unsigned short, hi) |
+                   ((unsigned)__builtin_bit_cast(unsigned short, lo) << 16);
       }
-      XTC_LDS_DONE();
-      prev = (bt * nloc + cl) * PV_CHUNK + j * 512;
     }
-  }
-  __syncthreads();
-  pv[prev + tid] = ST[512 + tid];   // the last k-step (j = 7) staged in buffer 1
-  pv[prev + 256 + tid] = ST[512 + 256 + tid];
+    // lanes kk = 2p and 2p + 1 (adjacent lanes) trade values so that each writes whole
+    // 32-bit words: the even lane elements (2p, 2p + 1) of bra 2 q, the odd lane those of
+    // bra 2 q + 1
+    const bool odd = kk & 1;
+    unsigned* dw = (unsigned*)(STh + (t & 1) * 4096);
+    const int bw = 2 * q2 + (odd ? 1 : 0);
+    const int slot = bw + 32 * (kk >> 3);
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const unsigned mine = odd ? pk[1][c] : pk[0][c];
+      const unsigned other = (unsigned)__builtin_amdgcn_update_dpp(   // of the lane beside it
+          0, (int)(odd ? pk[0][c] : pk[1][c]), 0xB1, 0xf, 0xf, true);
+      const unsigned e0 = odd ? other : mine, e1 = odd ? mine : other;   // kets 2p, 2p + 1
+      dw[(((c * 2 + 0) * 64 + slot) * 8 + (kk & 6)) / 2] = (e0 & 0xffffu) | (e1 << 16);
+      dw[(((c * 2 + 1) * 64 + slot) * 8 + (kk & 6)) / 2] = (e0 >> 16) | (e1 & 0xffff0000u);
+    }
+  };
+  const int nsteps = (int)(cl1 - cl0) * 8;
+  bh_ket_steps(L, T, xyz, n_g, kbeg, nsteps, nn, tid, top, pairs);
+  out += (nsteps - 1) * 512;   // the last k-step, staged in buffer 1
+  out[tid] = ST[512 + tid];
+  out[256 + tid] = ST[512 + 256 + tid];
+  XTC_LDS_DONE();
   __syncthreads();
   double* red = sm;   // [8 sums][32 bras][16 kets], over the tables and the staging
 #pragma unroll
@@ -299,7 +349,7 @@ __global__ __launch_bounds__(256) void k_bh_pairs(
 // launch and 64-bra tile t: pv64[t][s][q][c][gk][gb] for the pair (bra gb, ket 4 gk + q).
 // The grid covers whole 64-bra tiles (two 32-bra halves; bras past the range repeat its
 // last point).
-__global__ __launch_bounds__(256) void k_bh_pairs_f64(const double* __restrict__ xyz, long n_g,
+__global__ __launch_bounds__(256, 2) void k_bh_pairs_f64(const double* __restrict__ xyz, long n_g,
                                                       long b0, long bn, long c0, long nloc,
                                                       EECoef cf, const BHTable* __restrict__ T,
                                                       double* __restrict__ pv64) {
@@ -325,27 +375,28 @@ __global__ __launch_bounds__(256) void k_bh_pairs_f64(const double* __restrict__
   // this thread's slot in a step: bra 64 (bt % 2) + 2 q2 + v of tile bt / 2, ket 4 gk + q
   double* dst = pv64 + (bt >> 1) * nsteps * 4096 + (kk & 3) * 1024 + (kk >> 2) * 64 +
                 (bt & 1) * 32 + 2 * q2;
-  for (long cl = cl0; cl < cl1; ++cl) {
-    for (int j = 0; j < 8; ++j) {
-      const long k0 = (c0 + cl) * SKC + 16 * j;
-      __syncthreads();
-      bh_fill_ket_tables(L, T, xyz, n_g, k0, nn, tid);
-      __syncthreads();
-      long g = k0 + kk;
-      if (g > n_g - 1) g = n_g - 1;   // padding kets: finite values; their A is zero
-      const double kx = xyz[g], ky = xyz[n_g + g], kz = xyz[2 * n_g + g];
-      double F[2][BH_NO], GF[2][BH_NO][3];
-      bh_two_pairs(L, nn, q2, kk, F, GF);
-      double* d = dst + (cl * 8 + j) * 4096;
+  const long kbeg = (c0 + cl0) * SKC;
+  double kx, ky, kz;
+  auto top = [&](int t) {
+    long g = kbeg + 16L * t + kk;
+    if (g > n_g - 1) g = n_g - 1;   // padding kets: finite values; their A is zero
+    kx = xyz[g];
+    ky = xyz[n_g + g];
+    kz = xyz[2 * n_g + g];
+  };
+  auto pairs = [&](int t) {
+    double F[2][BH_NO], GF[2][BH_NO][3];
+    bh_two_pairs(L, L.TK + (t & 1) * 16 * L.ks, nn, q2, kk, F, GF);
+    double* d = dst + (cl0 * 8 + t) * 4096;
 #pragma unroll
-      for (int v = 0; v < 2; ++v) {
-        double o[4];
-        bh_finish(cf, F[v], GF[v], xb[v] - kx, yb[v] - ky, zb[v] - kz, o);
+    for (int v = 0; v < 2; ++v) {
+      double o[4];
+      bh_finish(cf, F[v], GF[v], xb[v] - kx, yb[v] - ky, zb[v] - kz, o);
 #pragma unroll
-        for (int c = 0; c < 4; ++c) d[c * 256 + v] = o[c];
-      }
+      for (int c = 0; c < 4; ++c) d[c * 256 + v] = o[c];
     }
-  }
+  };
+  bh_ket_steps(L, T, xyz, n_g, kbeg, (int)(cl1 - cl0) * 8, nn, tid, top, pairs);
 }
 
 size_t bh_f64_pv_bytes(long bp) {
