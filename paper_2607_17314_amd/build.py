@@ -39,6 +39,7 @@ FLAGS = [
 # compiler on the BH form's FP64 stage-1 kernel (stage1_f64.hip).
 FILE_FLAGS = {
     "gemm_f64.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
+    "solve.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
     "grad.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
     "stage1_products.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
 }

@@ -141,14 +141,6 @@ __global__ void k_square(double* __restrict__ x, long n) {
   if (t < n) x[t] = x[t] * x[t];
 }
 
-__global__ void k_copy_rows(const double* __restrict__ src, long lds, double* __restrict__ dst,
-                            long ldd, int rows, long cols) {
-  long t = (long)blockIdx.x * 256 + threadIdx.x;
-  if (t >= (long)rows * cols) return;
-  long r = t / cols, c = t % cols;
-  dst[r * ldd + c] = src[r * lds + c];
-}
-
 // per grid point of a chunk: w^2 (|m_g|^2 - |y_g|^2) and w^2 |m_g|^2, channel c (-1 scalar)
 __global__ void k_resid(const double* __restrict__ phi4, const double* __restrict__ w, long n_g,
                         int n_orb, int comp, long g0, long cn, const double* __restrict__ y,
@@ -273,67 +265,16 @@ struct Factor {
   const double* L; const double* linv; long n; int nblk;
 };
 
-// Forward substitution L Y = R for the columns of a chunk (R: [n][cn], row stride ldr, used
-// as scratch); Y goes to out (row stride ldo).
-static xtc_status solve_chunk(const Factor& f, long cn, double* R, long ldr, double* out, long ldo,
-                              hipStream_t st) {
-  const long n = f.n;
-  // forward: Y_i = Linv_ii (R_i - L_i,<i Y_<i), Y stored in out
-  for (int b = 0; b < f.nblk; ++b) {
-    long i0 = (long)b * NB;
-    long nb = (n - i0) < NB ? (n - i0) : NB;
-    if (i0 > 0) {
-      GemmArgs g{};
-      g.M = nb; g.N = cn; g.K = i0;
-      g.A = f.L + i0 * n; g.a_sm = n; g.a_sk = 1;
-      g.B = out; g.b_sk = ldo; g.b_sn = 1;
-      g.C = R + i0 * ldr; g.c_sm = ldr; g.c_sn = 1;
-      g.alpha = -1.0; g.beta = 1.0;
-      XTC_TRY(gemm_f64(g, st));
-    }
-    GemmArgs d{};
-    d.M = nb; d.N = cn; d.K = nb;
-    d.A = f.linv + (long)b * NB * NB; d.a_sm = NB; d.a_sk = 1;
-    d.B = R + i0 * ldr; d.b_sk = ldr; d.b_sn = 1;
-    d.C = out + i0 * ldo; d.c_sm = ldo; d.c_sn = 1;
-    XTC_TRY(gemm_f64(d, st));
-  }
-  return XTC_OK;
+// Forward substitution L Y = R for the columns of a chunk (R: [n][cn], row stride ldr); Y goes
+// to out (row stride ldo).
+static xtc_status solve_chunk(const Factor& f, long cn, const double* R, long ldr, double* out,
+                              long ldo, hipStream_t st) {
+  return solve_columns(f.L, f.linv, f.n, cn, R, ldr, out, ldo, false, st);
 }
 
-// Back substitution L^T X = Y in place in out (row stride ldo); R [n][cn] (row stride ldr)
-// is scratch.
-static xtc_status back_chunk(const Factor& f, long cn, double* R, long ldr, double* out, long ldo,
-                             hipStream_t st) {
-  const long n = f.n;
-  for (int b = f.nblk - 1; b >= 0; --b) {
-    long i0 = (long)b * NB;
-    long nb = (n - i0) < NB ? (n - i0) : NB;
-    long i1 = i0 + nb;
-    if (i1 < n) {
-      GemmArgs g{};   // R_i = Y_i - L_{>i,i}^T X_{>i}
-      g.M = nb; g.N = cn; g.K = n - i1;
-      g.A = f.L + i1 * n + i0; g.a_sm = 1; g.a_sk = n;
-      g.B = out + i1 * ldo; g.b_sk = ldo; g.b_sn = 1;
-      g.C = R + i0 * ldr; g.c_sm = ldr; g.c_sn = 1;
-      g.alpha = -1.0; g.beta = 1.0;   // R_i holds a copy of Y_i (below)
-      hipLaunchKernelGGL(k_copy_rows, dim3(cdiv(nb * cn, 256)), dim3(256), 0, st,
-                         (const double*)(out + i0 * ldo), ldo, R + i0 * ldr, ldr, (int)nb, cn);
-      XTC_CHECK_LAUNCH();
-      XTC_TRY(gemm_f64(g, st));
-    } else {
-      hipLaunchKernelGGL(k_copy_rows, dim3(cdiv(nb * cn, 256)), dim3(256), 0, st,
-                         (const double*)(out + i0 * ldo), ldo, R + i0 * ldr, ldr, (int)nb, cn);
-      XTC_CHECK_LAUNCH();
-    }
-    GemmArgs d{};   // X_i = Linv_ii^T R_i
-    d.M = nb; d.N = cn; d.K = nb;
-    d.A = f.linv + (long)b * NB * NB; d.a_sm = 1; d.a_sk = NB;
-    d.B = R + i0 * ldr; d.b_sk = ldr; d.b_sn = 1;
-    d.C = out + i0 * ldo; d.c_sm = ldo; d.c_sn = 1;
-    XTC_TRY(gemm_f64(d, st));
-  }
-  return XTC_OK;
+// Back substitution L^T X = Y in place in out (row stride ldo).
+static xtc_status back_chunk(const Factor& f, long cn, double* out, long ldo, hipStream_t st) {
+  return solve_columns(f.L, f.linv, f.n, cn, out, ldo, out, ldo, true, st);
 }
 
 static Factor factor_of(const FitLayout& F, long n) { return Factor{F.A, F.linv, n, F.nblk}; }
@@ -485,7 +426,7 @@ xtc_status fit_columns(const double* phi4, long n_g, int n_orb, const double* ph
   const Factor f{chol_sys, chol_sys + n * n, n, (int)cdiv(n, NB)};
   XTC_TRY(rhs_chunk(phi4, n_g, n_orb, phimu, n, sys - 1, g0, cn, P, R, ldr, st));
   XTC_TRY(solve_chunk(f, cn, R, ldr, out, ldo, st));
-  return back_chunk(f, cn, R, ldr, out, ldo, st);
+  return back_chunk(f, cn, out, ldo, st);
 }
 
 xtc_status gather_pivot_rows(const double* phi4, long n_g, int rows, const long* piv, int n_mu,
@@ -606,7 +547,7 @@ extern "C" xtc_status isdf_fit(const double* phi4, const xtc_grid* grid, int32_t
       XTC_CHECK_LAUNCH();
       XTC_TRY(reduce_sum_f64(F.rtx[l], cn, F.sums + 2 * c, F.redx[l], sl));
       XTC_TRY(reduce_sum_f64(F.mtx[l], cn, F.sums + 2 * c + 1, F.redx[l], sl));
-      XTC_TRY(back_chunk(factor_of(F, n), cn, F.Rx[l], F.chunk, out, ldo, sl));
+      XTC_TRY(back_chunk(factor_of(F, n), cn, out, ldo, sl));
       if (sys == 0 && rhot) {   // ISDF density from the FP64 solution (the product the
         GemmArgs g{};           // contraction forms from FP64 xi, element for element)
         g.M = 1; g.N = cn; g.K = n;
