@@ -33,85 +33,115 @@ __global__ void k_gather_piv(const double* __restrict__ phi4, long n_g, int rows
 // Factor the NB x NB diagonal block at (j0, j0) of the n x n matrix a (row-major,
 // lower triangle used) in LDS, write L_jj back (upper part zeroed) and its
 // inverse to linv [NB][NB]; a non-positive or non-finite pivot sets *fail.
-// One workgroup of 256 threads as 16 x 16. The factorisation runs column by column
-// (right-looking, the trailing update spread over the 16 x 16 threads); the inverse
-// goes by 16 x 16 blocks: the four diagonal blocks first (one column per thread),
-// then the blocks below the diagonal by block diagonals,
+// One workgroup of 256 threads. The factorisation goes by panels of PB columns: wave 0
+// factors one with a row per lane and the panel's columns in its registers (pivots and
+// multipliers by readlane, no barrier), then all threads update the block right of it, PB
+// products at a time. The inverse goes by PB x PB blocks: the four diagonal blocks first
+// (one column per thread, in registers), then the blocks below the diagonal by block
+// diagonals,
 //   X_IJ = -inv(L_II) sum_{J <= K < I} L_IK X_KJ,
-// so that its longest dependent chain is ~300 products instead of ~NB^2 / 2.
-constexpr int PB = 16;   // inverse block
+// in runs of PB products whose operands are all read ahead.
+// Bound: one chain of 64 square roots and reciprocals (each ~300 cycles of dependent
+// instructions) and the panel updates between them; every product is added in the order of
+// the column-by-column form. With that form's three barriers per column and its inner
+// products reading LDS in their chains: 60.3 -> 29.6 us per block.
+constexpr int PB = 16;
+
+__device__ __forceinline__ double lane_value(double v, int lane) {
+  const unsigned long long u = __builtin_bit_cast(unsigned long long, v);
+  const unsigned lo = __builtin_amdgcn_readlane((unsigned)u, lane);
+  const unsigned hi = __builtin_amdgcn_readlane((unsigned)(u >> 32), lane);
+  return __builtin_bit_cast(double, (unsigned long long)hi << 32 | lo);
+}
 
 __global__ __launch_bounds__(256) void k_potrf_diag(double* __restrict__ a, long n, long j0,
                                                     int nb, double* __restrict__ linv,
                                                     int* __restrict__ fail) {
-  static_assert(NB == 4 * PB, "the inverse works on 4 x 4 blocks of 16");
+  static_assert(NB == 4 * PB && NB == 64, "four panels of 16, a row per lane of a wave");
   __shared__ double s[NB][NB + 1];
   __shared__ double sinv[NB][NB + 1];
   __shared__ double tmp[NB][NB + 1];
   __shared__ double rdiag[NB];
-  __shared__ int bad;
   const int t = threadIdx.x, tx = t & 15, ty = t >> 4;
-  if (t == 0) bad = 0;
+  bool bad = false;
+  // rows and columns past nb: unit diagonal
   for (int e = t; e < NB * NB; e += 256) {
     const int i = e / NB, k = e % NB;
-    s[i][k] = (i < nb && k < nb && k <= i) ? a[(j0 + i) * n + j0 + k] : 0.0;
+    s[i][k] = (i < nb && k <= i) ? a[(j0 + i) * n + j0 + k] : (i == k ? 1.0 : 0.0);
     sinv[i][k] = 0.0;
   }
-  // padding rows and columns past nb: unit diagonal, so the blocked inverse stays regular
-  if (t < NB && t >= nb) s[t][t] = 1.0;
   __syncthreads();
-  for (int j = 0; j < nb; ++j) {
-    if (t == 0) {
-      double v = s[j][j];
-      if (!(v > 0.0) || !isfinite(v)) {
-        bad = 1;
-        v = 1.0;
+  for (int p0 = 0; p0 < NB; p0 += PB) {
+    if (t < NB) {   // wave 0: lane t has row t of the panel
+      double c[PB];
+#pragma unroll
+      for (int j = 0; j < PB; ++j) c[j] = s[t][p0 + j];
+#pragma unroll
+      for (int j = 0; j < PB; ++j) {
+        double v = lane_value(c[j], p0 + j);
+        if (!(v > 0.0) || !isfinite(v)) {
+          bad = true;
+          v = 1.0;
+        }
+        const double d = sqrt(v), rj = 1.0 / d;
+        c[j] = t == p0 + j ? d : c[j] * rj;
+        if (t == p0 + j) rdiag[t] = rj;
+        // (i, k) of the panel, j < k <= i; the lanes above the diagonal hold nothing in use
+#pragma unroll
+        for (int k = j + 1; k < PB; ++k) c[k] -= c[j] * lane_value(c[j], p0 + k);
       }
-      const double d = sqrt(v);
-      s[j][j] = d;
-      rdiag[j] = 1.0 / d;
+#pragma unroll
+      for (int j = 0; j < PB; ++j)
+        if (t >= p0 + j) s[t][p0 + j] = c[j];
     }
     __syncthreads();
-    const double rj = rdiag[j];
-    for (int i = j + 1 + t; i < nb; i += 256) s[i][j] *= rj;
-    __syncthreads();
-    // trailing update of (i, k), j < k <= i < nb
-    for (int i = j + 1 + ty; i < nb; i += 16) {
-      const double sij = s[i][j];
-      for (int k = j + 1 + tx; k <= i; k += 16) s[i][k] -= sij * s[k][j];
-    }
+    // (i, k), p0 + PB <= k <= i, less the panel's products in the order of its columns
+    const int r0 = p0 + PB + ty, c0 = p0 + PB + tx;
+    const int left = (NB - p0) / PB - 1;   // 16 x 16 blocks a side
+    for (int bi = 0; bi < left; ++bi)
+      for (int bk = 0; bk <= bi; ++bk) {
+        double x = s[r0 + PB * bi][c0 + PB * bk];
+#pragma unroll
+        for (int j = 0; j < PB; ++j) x -= s[r0 + PB * bi][p0 + j] * s[c0 + PB * bk][p0 + j];
+        if (c0 + PB * bk <= r0 + PB * bi) s[r0 + PB * bi][c0 + PB * bk] = x;
+      }
     __syncthreads();
   }
-  for (int i = t; i < NB; i += 256)
-    if (i >= nb) rdiag[i] = 1.0;
-  __syncthreads();
-  // diagonal blocks: thread (block b = ty / 4 .. , column) -- 64 threads, one column each
+  // diagonal blocks of the inverse: thread t column t
   if (t < NB) {
-    const int b = t / PB, c = t;
-    const int r0 = b * PB;
-    for (int i = c; i < r0 + PB; ++i) {
-      double v = (i == c) ? 1.0 : 0.0;
-      for (int k = c; k < i; ++k) v -= s[i][k] * sinv[k][c];
-      sinv[i][c] = v * rdiag[i];
+    const int c = t & (PB - 1), r0 = t - c;
+    double x[PB];
+#pragma unroll
+    for (int i = 0; i < PB; ++i) {
+      double v = i == c ? 1.0 : 0.0;
+#pragma unroll
+      for (int k = 0; k < i; ++k) v -= s[r0 + i][r0 + k] * x[k];   // x[k] = 0 above the diagonal
+      x[i] = i < c ? 0.0 : v * rdiag[r0 + i];
     }
+#pragma unroll
+    for (int i = 0; i < PB; ++i) sinv[r0 + i][t] = x[i];
   }
   __syncthreads();
   // block diagonals d = 1, 2, 3: T_IJ = sum_{J <= K < I} L_IK X_KJ, then X_IJ = -inv(L_II) T_IJ
+  // (whole blocks: inv(L_II) is zero above its diagonal)
+  auto run = [&](double v, const double* row, const double* col) {
+#pragma unroll
+    for (int k = 0; k < PB; ++k) v += row[k] * col[k * (NB + 1)];
+    return v;
+  };
   for (int d = 1; d < 4; ++d) {
     for (int J = 0; J + d < 4; ++J) {
       const int I = J + d;
       const int r = I * PB + ty, c = J * PB + tx;
       double v = 0.0;
-      for (int k = J * PB; k < I * PB; ++k) v += s[r][k] * sinv[k][c];
+      for (int K = J; K < I; ++K) v = run(v, &s[r][K * PB], &sinv[K * PB][c]);
       tmp[r][c] = v;
     }
     __syncthreads();
     for (int J = 0; J + d < 4; ++J) {
       const int I = J + d;
       const int r = I * PB + ty, c = J * PB + tx;
-      double v = 0.0;
-      for (int k = I * PB; k <= r; ++k) v += sinv[r][k] * tmp[k][c];
-      sinv[r][c] = -v;
+      sinv[r][c] = -run(0.0, &sinv[r][I * PB], &tmp[I * PB][c]);
     }
     __syncthreads();
   }
@@ -141,35 +171,35 @@ __global__ void k_square(double* __restrict__ x, long n) {
   if (t < n) x[t] = x[t] * x[t];
 }
 
+// sum of x[i stride]^2, in the order of i, 32 values requested at a time
+__device__ __forceinline__ double sum_squares(const double* x, long stride, int n) {
+  constexpr int U = 32;
+  double sum = 0.0;
+  int i = 0;
+  for (; i + U <= n; i += U) {
+    double v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) v[u] = x[(long)(i + u) * stride];
+#pragma unroll
+    for (int u = 0; u < U; ++u) sum += v[u] * v[u];
+  }
+  for (; i < n; ++i) sum += x[(long)i * stride] * x[(long)i * stride];
+  return sum;
+}
+
+// One thread per point, so few waves: bound by the latency of the loads (1,500 rows, 58,200
+// points, one load in flight each: 718 us, 32: 157).
 // per grid point of a chunk: w^2 (|m_g|^2 - |y_g|^2) and w^2 |m_g|^2, channel c (-1 scalar)
 __global__ void k_resid(const double* __restrict__ phi4, const double* __restrict__ w, long n_g,
                         int n_orb, int comp, long g0, long cn, const double* __restrict__ y,
                         long ldy, int n_mu, double* __restrict__ r_out,
                         double* __restrict__ m_out) {
-  long t = (long)blockIdx.x * 256 + threadIdx.x;
+  long t = (long)blockIdx.x * 64 + threadIdx.x;
   if (t >= cn) return;
   long g = g0 + t;
-  double n2 = 0.0;
-  for (int p = 0; p < n_orb; ++p) {
-    double v = phi4[(long)p * n_g + g];
-    n2 += v * v;
-  }
-  double m2;
-  if (comp < 0) {
-    m2 = n2 * n2;
-  } else {
-    double g2 = 0.0;
-    for (int p = 0; p < n_orb; ++p) {
-      double v = phi4[(long)((1 + comp) * n_orb + p) * n_g + g];
-      g2 += v * v;
-    }
-    m2 = n2 * g2;
-  }
-  double yy = 0.0;
-  for (int m = 0; m < n_mu; ++m) {
-    double v = y[(long)m * ldy + t];
-    yy += v * v;
-  }
+  const double n2 = sum_squares(phi4 + g, n_g, n_orb);
+  const double m2 = n2 * (comp < 0 ? n2 : sum_squares(phi4 + (long)(1 + comp) * n_orb * n_g + g, n_g, n_orb));
+  const double yy = sum_squares(y + t, ldy, n_mu);
   double ww = w[g] * w[g];
   r_out[t] = ww * (m2 - yy);
   m_out[t] = ww * m2;
@@ -280,17 +310,17 @@ static xtc_status back_chunk(const Factor& f, long cn, double* out, long ldo, hi
 static Factor factor_of(const FitLayout& F, long n) { return Factor{F.A, F.linv, n, F.nblk}; }
 
 // The right-hand side of one system for grid points [g0, g0 + cn) into R (row stride ldr),
-// with P (row stride ldr) as scratch: B = P o P (scalar, comp -1) or (dPhi_mu^T dPhi)_c o P,
+// with P (row stride ldr) as scratch (have_p: the chunk's P is in it): B = P o P (scalar, comp -1) or (dPhi_mu^T dPhi)_c o P,
 // P = Phi_mu^T Phi. phimu: [4][n_orb][n_mu], the orbitals and gradients at the pivots.
 static xtc_status rhs_chunk(const double* phi4, long n_g, int n_orb, const double* phimu, long n,
                             int comp, long g0, long cn, double* P, double* R, long ldr,
-                            hipStream_t st) {
+                            hipStream_t st, bool have_p = false) {
   GemmArgs p{};   // P = Phi_mu^T Phi (chunk)
   p.M = n; p.N = cn; p.K = n_orb;
   p.A = phimu; p.a_sm = 1; p.a_sk = n;
   p.B = phi4 + g0; p.b_sk = n_g; p.b_sn = 1;
   p.C = P; p.c_sm = ldr; p.c_sn = 1;
-  XTC_TRY(gemm_f64(p, st));
+  if (!have_p) XTC_TRY(gemm_f64(p, st));
   GemmArgs r{};   // B = P o P or (dPhi_mu^T dPhi)_c o P
   r.M = n; r.N = cn; r.K = n_orb;
   const double* ph = phimu + (long)(comp < 0 ? 0 : (1 + comp)) * n_orb * n;
@@ -380,7 +410,7 @@ xtc_status fit_residuals(const double* phi4, const xtc_grid* grid, int n_orb,
       const long cn = (n_g - g0) < F.chunk ? (n_g - g0) : F.chunk;
       XTC_TRY(rhs_chunk(phi4, n_g, n_orb, F.phimu, n, comp, g0, cn, F.P, F.R, F.chunk, st));
       XTC_TRY(solve_chunk(factor_of(F, n), cn, F.R, F.chunk, F.P, F.chunk, st));  // Y into F.P
-      hipLaunchKernelGGL(k_resid, dim3(cdiv(cn, 256)), dim3(256), 0, st, phi4, grid->w, n_g, n_orb,
+      hipLaunchKernelGGL(k_resid, dim3(cdiv(cn, 64)), dim3(64), 0, st, phi4, grid->w, n_g, n_orb,
                          comp, g0, cn, (const double*)F.P, F.chunk, n_mu, F.rtmp, F.mtmp);
       XTC_CHECK_LAUNCH();
       XTC_TRY(reduce_sum_f64(F.rtmp, cn, F.sums + 2 * c, F.red, st));
@@ -498,6 +528,7 @@ extern "C" xtc_status isdf_fit(const double* phi4, const xtc_grid* grid, int32_t
   double jit[4] = {-1, -1, -1, -1}, rel[4] = {0, 0, 0, 0};
   bool any_jitter = false;
   const bool keep = (what & XTC_FIT_KEEP_CHOL) != 0;
+  bool have_p = false;   // every lane has one chunk, whose P is still there from the last system
   for (int sys = 0; sys < 4; ++sys) {
     const int comp = sys - 1;   // -1 scalar, 0..2 gradient component
     const bool solve = sys == 0 ? (what & XTC_FIT_XI) != 0 : (what & XTC_FIT_XIGRAD) != 0;
@@ -540,9 +571,10 @@ extern "C" xtc_status isdf_fit(const double* phi4, const xtc_grid* grid, int32_t
       long cn = (n_g - g0) < F.chunk ? (n_g - g0) : F.chunk;
       double* out = f32 ? F.Px[l] : (sys == 0 ? (double*)xi : xigrad + (long)comp * n * n_g) + g0;
       const long ldo = f32 ? F.chunk : n_g;
-      XTC_TRY(rhs_chunk(phi4, n_g, n_orb, F.phimu, n, comp, g0, cn, F.Px[l], F.Rx[l], F.chunk, sl));
+      XTC_TRY(rhs_chunk(phi4, n_g, n_orb, F.phimu, n, comp, g0, cn, F.Px[l], F.Rx[l], F.chunk, sl,
+                        have_p));
       XTC_TRY(solve_chunk(factor_of(F, n), cn, F.Rx[l], F.chunk, out, ldo, sl));
-      hipLaunchKernelGGL(k_resid, dim3(cdiv(cn, 256)), dim3(256), 0, sl, phi4, grid->w, n_g,
+      hipLaunchKernelGGL(k_resid, dim3(cdiv(cn, 64)), dim3(64), 0, sl, phi4, grid->w, n_g,
                          n_orb, comp, g0, cn, (const double*)out, ldo, n_mu, F.rtx[l], F.mtx[l]);
       XTC_CHECK_LAUNCH();
       XTC_TRY(reduce_sum_f64(F.rtx[l], cn, F.sums + 2 * c, F.redx[l], sl));
@@ -562,6 +594,7 @@ extern "C" xtc_status isdf_fit(const double* phi4, const xtc_grid* grid, int32_t
         XTC_CHECK_LAUNCH();
       }
     }
+    have_p = F.nchunks == F.lanes && !f32;
     for (int l = 1; l < F.lanes; ++l) {
       XTC_HIP(hipEventRecord(evs.ev[l], ls[l]));
       XTC_HIP(hipStreamWaitEvent(st, evs.ev[l], 0));
