@@ -86,18 +86,29 @@ __global__ __launch_bounds__(256) void k_row_exp(SegOperand o, long rows, int* _
     for (int sg = 0; sg < o.nseg; ++sg) {
       const double* X = o.X[sg] ? o.X[sg] + r * o.sm : nullptr;
       const double* sc = o.s[sg];
-      // FP64 rows that start on a 16-byte boundary: two values per load (the maximum does
-      // not depend on the order it is taken in)
+      // FP64 rows that start on a 16-byte boundary: two values per load, eight loads in flight
+      // (the maximum does not depend on the order it is taken in). Bound by reading the rows:
+      // 1,500 rows of up to 16,384, mean of ten-atom launches, 102 us with one load in flight,
+      // 67 with eight
       if (X && !o.Xf[sg] && ((uintptr_t)X & 15) == 0 && (!sc || ((uintptr_t)sc & 15) == 0)) {
+        constexpr int U = 8;
         const long K2 = o.K / 2;
-        for (long k = threadIdx.x; k < K2; k += 256) {
-          double2 v = ((const double2*)X)[k];
-          if (sc) {
-            const double2 t = ((const double2*)sc)[k];
-            v.x *= t.x;
-            v.y *= t.y;
+        for (long k = threadIdx.x; k < K2; k += 256 * U) {
+          double2 v[U], t[U];
+#pragma unroll
+          for (int u = 0; u < U; ++u) {   // past the end: the last pair again
+            const long i = k + 256 * u < K2 ? k + 256 * u : K2 - 1;
+            v[u] = ((const double2*)X)[i];
+            if (sc) t[u] = ((const double2*)sc)[i];
           }
-          m = fmax(m, fmax(fabs(v.x), fabs(v.y)));
+#pragma unroll
+          for (int u = 0; u < U; ++u) {
+            if (sc) {
+              v[u].x *= t[u].x;
+              v[u].y *= t[u].y;
+            }
+            m = fmax(m, fmax(fabs(v[u].x), fabs(v[u].y)));
+          }
         }
         if ((o.K & 1) && threadIdx.x == 0) m = fmax(m, fabs(seg_value(o, sg, r, o.K - 1)));
       } else {
