@@ -947,7 +947,18 @@ __global__ __launch_bounds__(64) void k_vmc_energy_bh(VmcDev v, VmcBH bh_in,
 
 // ---------------------------------------------------------------------------------------
 // Gauss-Newton step (eq. gn) on the clipped variance (eq. var-loss), one workgroup of
-// VMC_GN_THREADS threads.
+// VMC_GN_THREADS threads. Every sum has one order: over the walkers of a thread in turn, then
+// a tree or the segments in turn; an entry of C above GN_FEW parameters over all walkers in
+// turn. Bound: the latency of one workgroup, so above GN_FEW parameters the loads go out in
+// runs ahead of the sums, and the factorisation has a thread per row. 50 parameters of 8,192
+// walkers 2,725 -> 1,315 us, 128 of 8,192 23.0 -> 3.5 ms (against tiles loaded between two
+// barriers, one row of four entries per thread and step, the factorisation on one thread).
+struct GnShared {
+  double red[VMC_GN_THREADS];
+  double dm[VMC_MAX_THETA], dmad[VMC_MAX_THETA], mdt[VMC_MAX_THETA], grad[VMC_MAX_THETA];
+  double C[VMC_MAX_THETA * VMC_MAX_THETA];
+  double x[VMC_MAX_THETA];
+};
 __device__ double gn_block_sum(double x, double* red) {
   const int t = threadIdx.x;
   red[t] = x;
@@ -961,30 +972,26 @@ __device__ double gn_block_sum(double x, double* red) {
   return s;
 }
 
-struct GnShared {
-  double red[VMC_GN_THREADS];
-  double dm[VMC_MAX_THETA], dmad[VMC_MAX_THETA], mdt[VMC_MAX_THETA], grad[VMC_MAX_THETA];
-  double C[VMC_MAX_THETA * VMC_MAX_THETA];
-  double x[VMC_MAX_THETA];
-};
-
 __global__ __launch_bounds__(VMC_GN_THREADS) void k_vmc_gn(const double* __restrict__ E,
                                                            const double* __restrict__ dE, long N,
                                                            int nth, double lam, double eta,
                                                            double* __restrict__ delta,
                                                            double* __restrict__ stats) {
-  __shared__ GnShared sh;
+  __shared__ __align__(16) GnShared sh;
   const int t = threadIdx.x;
   const double inv_n = 1.0 / (double)N;
   double a = 0.0;
+#pragma unroll 8
   for (long k = t; k < N; k += VMC_GN_THREADS) a += E[k];
   const double m = gn_block_sum(a, sh.red) * inv_n;
   a = 0.0;
+#pragma unroll 8
   for (long k = t; k < N; k += VMC_GN_THREADS) a += fabs(E[k] - m);
   const double mad = gn_block_sum(a, sh.red) * inv_n;
   const double lo = m - 5.0 * mad, hi = m + 5.0 * mad;
   a = 0.0;
   double ncl = 0.0;
+#pragma unroll 8
   for (long k = t; k < N; k += VMC_GN_THREADS) {
     const double e = E[k];
     a += e < lo ? lo : (e > hi ? hi : e);
@@ -993,12 +1000,16 @@ __global__ __launch_bounds__(VMC_GN_THREADS) void k_vmc_gn(const double* __restr
   const double mean = gn_block_sum(a, sh.red) * inv_n;
   const double nclip = gn_block_sum(ncl, sh.red);
   a = 0.0;
+#pragma unroll 8
   for (long k = t; k < N; k += VMC_GN_THREADS) {
     const double e = E[k];
     const double r = (e < lo ? lo : (e > hi ? hi : e)) - mean;
     a += r * r;
   }
   const double var = gn_block_sum(a, sh.red) / (double)(N - 1);
+  auto dclip = [&](double e, double d, int p) {   // derivative p of a walker's clipped energy
+    return e < lo ? sh.dm[p] - 5.0 * sh.dmad[p] : (e > hi ? sh.dm[p] + 5.0 * sh.dmad[p] : d);
+  };
   if (nth <= GN_FEW) {
     // few parameters: each sum is one block reduction over the walkers
     // derivatives of m and of the MAD, then of the clipped energies
@@ -1020,15 +1031,10 @@ __global__ __launch_bounds__(VMC_GN_THREADS) void k_vmc_gn(const double* __restr
       if (t == 0) sh.dmad[p] = s * inv_n;
     }
     __syncthreads();
-    auto dclip = [&](long k, int p) {
-      const double e = E[k];
-      if (e < lo) return sh.dm[p] - 5.0 * sh.dmad[p];
-      if (e > hi) return sh.dm[p] + 5.0 * sh.dmad[p];
-      return dE[k * nth + p];
-    };
+    auto dclip_k = [&](long k, int p) { return dclip(E[k], dE[k * nth + p], p); };
     for (int p = 0; p < nth; ++p) {
       a = 0.0;
-      for (long k = t; k < N; k += VMC_GN_THREADS) a += dclip(k, p);
+      for (long k = t; k < N; k += VMC_GN_THREADS) a += dclip_k(k, p);
       const double s = gn_block_sum(a, sh.red);
       if (t == 0) sh.mdt[p] = s * inv_n;
     }
@@ -1039,7 +1045,7 @@ __global__ __launch_bounds__(VMC_GN_THREADS) void k_vmc_gn(const double* __restr
       for (long k = t; k < N; k += VMC_GN_THREADS) {
         const double e = E[k];
         const double r = (e < lo ? lo : (e > hi ? hi : e)) - mean;
-        a += (dclip(k, p) - sh.mdt[p]) * r;
+        a += (dclip_k(k, p) - sh.mdt[p]) * r;
       }
       const double s = gn_block_sum(a, sh.red);
       if (t == 0) sh.grad[p] = 2.0 * s / (double)(N - 1);
@@ -1048,7 +1054,7 @@ __global__ __launch_bounds__(VMC_GN_THREADS) void k_vmc_gn(const double* __restr
       for (int q = 0; q <= p; ++q) {
         a = 0.0;
         for (long k = t; k < N; k += VMC_GN_THREADS)
-          a += (dclip(k, p) - sh.mdt[p]) * (dclip(k, q) - sh.mdt[q]);
+          a += (dclip_k(k, p) - sh.mdt[p]) * (dclip_k(k, q) - sh.mdt[q]);
         const double s = gn_block_sum(a, sh.red);
         if (t == 0) {
           const double c = s * inv_n + (p == q ? lam : 0.0);
@@ -1058,152 +1064,189 @@ __global__ __launch_bounds__(VMC_GN_THREADS) void k_vmc_gn(const double* __restr
       }
     }
   } else {
-    // The parameter sums run in walker order over tiles of tk walkers: a tile's dE rows are
-    // staged in the space of C (not needed until the end) and its energies in red; one
-    // thread per parameter column, and up to GN_BLK blocks of C per thread, a block being the
-    // four entries (p, q0 .. q0 + 3), q0 a multiple of 4 not above p (one read of row p
-    // serves four products).
-    constexpr int GN_NBLK = VMC_MAX_THETA * (VMC_MAX_THETA / 4 + 1) / 2 + VMC_MAX_THETA;
-    constexpr int GN_BLK = (GN_NBLK + VMC_GN_THREADS - 1) / VMC_GN_THREADS;
+    // Column sums over the walkers: thread t takes column t % nth and, of every tile of tk
+    // walkers, those of segment t / nth (every S-th, S = threads / nth); the S partial sums of
+    // a column are then added in segment order (fixed).
     const int tk = VMC_MAX_THETA * VMC_MAX_THETA / nth < VMC_GN_THREADS
                        ? VMC_MAX_THETA * VMC_MAX_THETA / nth : VMC_GN_THREADS;
-    double* tile = sh.C;
-    double* te = sh.red;
-    auto stage = [&](long k0, int nk) {
-      __syncthreads();   // the previous tile's readers are done
-      for (int e = t; e < nk * nth; e += VMC_GN_THREADS) tile[e] = dE[k0 * nth + e];
-      for (int e = t; e < nk; e += VMC_GN_THREADS) te[e] = E[k0 + e];
-      __syncthreads();
-    };
-    auto tile_len = [&](long k0) { return (int)(N - k0 < tk ? N - k0 : tk); };
-    // Column sums over the walkers: thread t takes column t % nth and the walkers of
-    // segment t / nth (every S-th walker of each tile, S = threads / nth); the S partial
-    // sums of a column are then added in segment order (fixed).
     const int S = VMC_GN_THREADS / nth, ccol = t % nth, cseg = t / nth;
-    auto combine = [&](double a) {   // returns the column total on threads t < nth
+    auto colsum = [&](auto f) {   // the column total of f(sum, e, dE) on threads t < nth
+      constexpr int U = 16;
+      double v = 0.0;
+      int kk = cseg;
+      for (long k0 = 0; cseg < S && k0 < N;) {
+        double e[U], d[U];
+        bool in[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const long k = k0 + kk;
+          in[u] = k < N;
+          const long kc = in[u] ? k : N - 1;
+          e[u] = E[kc];
+          d[u] = dE[kc * nth + ccol];
+          kk += S;
+          if (kk >= tk) {
+            kk = cseg;
+            k0 += tk;
+          }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+          if (in[u]) f(v, e[u], d[u]);
+      }
       __syncthreads();
-      te[t] = cseg < S ? a : 0.0;
+      sh.red[t] = v;
       __syncthreads();
       double tot = 0.0;
       if (t < nth)
-        for (int g = 0; g < S; ++g) tot += te[g * nth + t];
+        for (int g = 0; g < S; ++g) tot += sh.red[g * nth + t];
       return tot;
     };
-    auto colsum = [&](auto f) {
-      double a = 0.0;
-      for (long k0 = 0; k0 < N; k0 += tk) {
-        const int nk = tile_len(k0);
-        stage(k0, nk);
-        if (cseg < S)
-          for (int kk = cseg; kk < nk; kk += S) a += f(kk, tile[kk * nth + ccol]);
-      }
-      return combine(a);
-    };
     // derivatives of m and of the MAD, then of the clipped energies
-    double a1 = colsum([&](int, double x) { return x; });
+    double a1 = colsum([&](double& v, double, double d) { v += d; });
     if (t < nth) sh.dm[t] = a1 * inv_n;
-    a1 = colsum([&](int kk, double x) {   // sh.dm is visible after the first tile's barrier
-      const double df = te[kk] - m;
-      return (df > 0.0 ? 1.0 : (df < 0.0 ? -1.0 : 0.0)) * (x - sh.dm[ccol]);
+    __syncthreads();
+    a1 = colsum([&](double& v, double e, double d) {
+      const double df = e - m;
+      v += (df > 0.0 ? 1.0 : (df < 0.0 ? -1.0 : 0.0)) * (d - sh.dm[ccol]);
     });
     if (t < nth) sh.dmad[t] = a1 * inv_n;
-    a1 = colsum([&](int kk, double x) {
-      const double e = te[kk];
-      return e < lo ? sh.dm[ccol] - 5.0 * sh.dmad[ccol]
-                    : (e > hi ? sh.dm[ccol] + 5.0 * sh.dmad[ccol] : x);
-    });
+    __syncthreads();
+    a1 = colsum([&](double& v, double e, double d) { v += dclip(e, d, ccol); });
     if (t < nth) sh.mdt[t] = a1 * inv_n;
+    __syncthreads();
     // residual r_k = Et_k - mean and dr_kp = dEt_kp - mean_k(dEt_kp): the gradient and C
-    int nblk = 0;   // blocks (p, q0), p-major
-    for (int pp = 0; pp < nth; ++pp) nblk += pp / 4 + 1;
-    const int nu = t < nblk ? (nblk - t + VMC_GN_THREADS - 1) / VMC_GN_THREADS : 0;
-    double cacc[GN_BLK][4];
-    int cp[GN_BLK], cq[GN_BLK];   // row p and first column q0 of this thread's blocks
-  #pragma unroll
-    for (int u = 0; u < GN_BLK; ++u) {
-      const int x = t + u * VMC_GN_THREADS;
-      int pp = 0, first = 0;
-      while (pp < nth && first + pp / 4 + 1 <= x) first += pp++ / 4 + 1;
-      cp[u] = x < nblk ? pp : 0;
-      cq[u] = x < nblk ? 4 * (x - first) : 0;
-      cacc[u][0] = cacc[u][1] = cacc[u][2] = cacc[u][3] = 0.0;
-    }
-    a1 = 0.0;
-    for (long k0 = 0; k0 < N; k0 += tk) {
-      const int nk = tile_len(k0);
-      stage(k0, nk);
-      for (int e = t; e < nk * nth; e += VMC_GN_THREADS) {   // centred clipped derivatives
-        const int kk = e / nth, p = e - kk * nth;
-        const double ev = te[kk];
-        const double v = ev < lo ? sh.dm[p] - 5.0 * sh.dmad[p]
-                                 : (ev > hi ? sh.dm[p] + 5.0 * sh.dmad[p] : tile[e]);
-        tile[e] = v - sh.mdt[p];
-      }
-      __syncthreads();
-      if (cseg < S)
-        for (int kk = cseg; kk < nk; kk += S) {
-          const double e0 = te[kk];
-          a1 += tile[kk * nth + ccol] * ((e0 < lo ? lo : (e0 > hi ? hi : e0)) - mean);
-        }
-      if (nu > 0)
-        for (int kk = 0; kk < nk; ++kk) {
-          const double* row = tile + kk * nth;
-  #pragma unroll
-          for (int u = 0; u < GN_BLK; ++u)   // the first test is block-uniform
-            if (u * VMC_GN_THREADS < nblk && u < nu) {
-              const double a = row[cp[u]];
-  #pragma unroll
-              for (int jq = 0; jq < 4; ++jq) {   // columns past the row's end are clamped, then dropped
-                const int q = cq[u] + jq < nth ? cq[u] + jq : nth - 1;
-                cacc[u][jq] += a * row[q];
-              }
-            }
-        }
-    }
-    a1 = combine(a1);
+    a1 = colsum([&](double& v, double e, double d) {
+      v += (dclip(e, d, ccol) - sh.mdt[ccol]) * ((e < lo ? lo : (e > hi ? hi : e)) - mean);
+    });
     if (t < nth) sh.grad[t] = 2.0 * a1 / (double)(N - 1);
+    // C by blocks of 4 x 4 entries (p, q), p's block not above q's, up to GN_BLK a thread; the
+    // walkers' dr rows (ld doubles, zeros past nth) pass through two buffers in the space that
+    // C takes at the end, the next tile loaded while the current one multiplies.
+    const int nq = (nth + 3) / 4, ld = 4 * nq, nblk = nq * (nq + 1) / 2;
+    constexpr int HALF = VMC_MAX_THETA * VMC_MAX_THETA / 2, GN_LOADS = HALF / VMC_GN_THREADS;
+    constexpr int MAXQ4 = VMC_MAX_THETA / 4;
+    constexpr int GN_BLK = (MAXQ4 * (MAXQ4 + 1) / 2 + VMC_GN_THREADS - 1) / VMC_GN_THREADS;
+    const int tl = HALF / ld;   // walkers of a tile
+    double cacc[GN_BLK][4][4];
+    int cp[GN_BLK], cq[GN_BLK];   // first row and column of this thread's blocks
+#pragma unroll
+    for (int u = 0; u < GN_BLK; ++u) {
+      int x = t + u * VMC_GN_THREADS, p = 0;
+      if (x >= nblk) x = 0;
+      while (x > p) x -= ++p;
+      cp[u] = 4 * p;
+      cq[u] = 4 * x;
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) cacc[u][i][j] = 0.0;
+    }
+    double ev[GN_LOADS], dv[GN_LOADS];
+    const int k_step = VMC_GN_THREADS / ld, p_step = VMC_GN_THREADS % ld;
+    auto each = [&](auto f) {   // (element, walker of the tile, parameter) of this thread's share
+      int kk = t / ld, p = t % ld;
+#pragma unroll
+      for (int i = 0; i < GN_LOADS; ++i) {
+        f(i, kk, p);
+        kk += k_step;
+        p += p_step;
+        if (p >= ld) {
+          p -= ld;
+          ++kk;
+        }
+      }
+    };
+    auto load = [&](long k0) {
+      each([&](int i, int kk, int p) {
+        const long k = k0 + kk < N ? k0 + kk : N - 1;
+        ev[i] = E[k];
+        dv[i] = dE[k * nth + (p < nth ? p : nth - 1)];
+      });
+    };
+    load(0);
+    __syncthreads();
+    int buf = 0;
+    for (long k0 = 0; k0 < N; k0 += tl, buf ^= 1) {
+      double* tile = sh.C + buf * HALF;
+      each([&](int i, int kk, int p) {
+        if (kk < tl) tile[kk * ld + p] = p < nth ? dclip(ev[i], dv[i], p) - sh.mdt[p] : 0.0;
+      });
+      if (k0 + tl < N) load(k0 + tl);
+      __syncthreads();   // the tile before this one is read to the end
+      const int nk = (int)(N - k0 < tl ? N - k0 : tl);
+#pragma unroll
+      for (int u = 0; u < GN_BLK; ++u)
+        if (t + u * VMC_GN_THREADS < nblk) {
+          const double* rp = tile + cp[u];
+          const double* rq = tile + cq[u];
+#pragma unroll 4
+          for (int kk = 0; kk < nk; ++kk) {
+            double vp[4], vq[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+              vp[i] = rp[kk * ld + i];
+              vq[i] = rq[kk * ld + i];
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+              for (int j = 0; j < 4; ++j) cacc[u][i][j] += vp[i] * vq[j];
+          }
+        }
+    }
     __syncthreads();   // the tile space becomes C
-  #pragma unroll
+#pragma unroll
     for (int u = 0; u < GN_BLK; ++u)
       if (t + u * VMC_GN_THREADS < nblk) {
-  #pragma unroll
-        for (int jq = 0; jq < 4; ++jq) {
-          const int pp = cp[u], qq = cq[u] + jq;
-          if (qq > pp) continue;   // q <= p < nth
-          const double c = cacc[u][jq] * inv_n + (pp == qq ? lam : 0.0);
-          sh.C[pp * nth + qq] = c;
-          sh.C[qq * nth + pp] = c;
-        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            const int pp = cp[u] + i, qq = cq[u] + j;
+            if (qq > pp || pp >= nth) continue;
+            const double c = cacc[u][i][j] * inv_n + (pp == qq ? lam : 0.0);
+            sh.C[pp * nth + qq] = c;
+            sh.C[qq * nth + pp] = c;
+          }
       }
   }
   __syncthreads();
-  if (t == 0) {
-    // Cholesky C = L L^T in place (lower), then L y = grad, L^T x = y, delta = -eta x
-    double info = 0.0;
-    for (int j = 0; j < nth && info == 0.0; ++j) {
-      double s = sh.C[j * nth + j];
-      for (int k = 0; k < j; ++k) s -= sh.C[j * nth + k] * sh.C[j * nth + k];
-      if (!(s > 0.0)) {
-        info = j + 1;
-        break;
-      }
-      const double ljj = sqrt(s);
-      sh.C[j * nth + j] = ljj;
-      for (int i = j + 1; i < nth; ++i) {
-        double v = sh.C[i * nth + j];
-        for (int k = 0; k < j; ++k) v -= sh.C[i * nth + k] * sh.C[j * nth + k];
-        sh.C[i * nth + j] = v / ljj;
-      }
+  // Cholesky C = L L^T in the upper triangle (L[i][k] at k nth + i, so that the rows of a
+  // column are neighbours): thread i row i, column by column
+  double info = 0.0;
+  for (int j = 0; j < nth; ++j) {
+    double v = 0.0;
+    if (t >= j && t < nth) {
+      v = sh.C[j * nth + t];
+#pragma unroll 8
+      for (int k = 0; k < j; ++k) v -= sh.C[k * nth + t] * sh.C[k * nth + j];
+      if (t == j) sh.red[0] = v;
     }
+    __syncthreads();
+    const double s = sh.red[0];
+    if (!(s > 0.0)) {
+      info = j + 1;
+      break;
+    }
+    const double ljj = sqrt(s);
+    if (t >= j && t < nth) sh.C[j * nth + t] = t == j ? ljj : v / ljj;
+    __syncthreads();
+  }
+  if (info == 0.0) {   // L y = grad (thread i row i), L^T x = y, delta = -eta x
+    double v = t < nth ? sh.grad[t] : 0.0;
+    for (int k = 0; k < nth; ++k) {
+      if (t == k) sh.x[k] = v / sh.C[k * nth + k];
+      __syncthreads();
+      if (t > k && t < nth) v -= sh.C[k * nth + t] * sh.x[k];
+    }
+  }
+  if (t == 0) {
     if (info == 0.0) {
-      for (int i = 0; i < nth; ++i) {
-        double v = sh.grad[i];
-        for (int k = 0; k < i; ++k) v -= sh.C[i * nth + k] * sh.x[k];
-        sh.x[i] = v / sh.C[i * nth + i];
-      }
       for (int i = nth - 1; i >= 0; --i) {
         double v = sh.x[i];
-        for (int k = i + 1; k < nth; ++k) v -= sh.C[k * nth + i] * sh.x[k];
+#pragma unroll 8
+        for (int k = i + 1; k < nth; ++k) v -= sh.C[i * nth + k] * sh.x[k];
         sh.x[i] = v / sh.C[i * nth + i];
       }
       for (int i = 0; i < nth; ++i) delta[i] = -eta * sh.x[i];
