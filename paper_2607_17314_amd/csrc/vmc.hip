@@ -416,7 +416,10 @@ __device__ __forceinline__ void vmc_ratios(const VmcDev& v, const double* A5, co
 // LDS (doubles): shell centres [n_cent][4], primitives [n_prim][2], A5 [5][n_el][n],
 // aug [n][2n], Ainv [2][n][n], chi [5][n_ao], part [5][64], fac [n], R [n_el][3], red [64];
 // then ints: shell records [n_shell][2], piv.
-__global__ __launch_bounds__(64) void k_vmc_energy(VmcDev v, EECoefV cf,
+// Two waves per SIMD: left alone the compiler takes 274 registers and one wave stays (20 atoms,
+// 16,384 walkers: 2,725 -> 2,441 us, five walkers per CU by LDS). The BH kernel is held to one
+// by its LDS there and only loses schedule by the limit (6.03 -> 6.75 ms for 8,192 walkers).
+__global__ __launch_bounds__(64, 2) void k_vmc_energy(VmcDev v, EECoefV cf,
                                                    const double* __restrict__ R, long n_w,
                                                    double* __restrict__ E,
                                                    double* __restrict__ dE) {
