@@ -1,8 +1,9 @@
 // Orbital and orbital-gradient values on the grid (Alg. 2, grid step).
-// One thread per grid point evaluates every AO value and Cartesian gradient of
-// a grid chunk into an SoA buffer ao4[4][n_ao][chunk]; the MO values follow as
+// One thread per grid point and shell group evaluates the AO values and Cartesian gradients
+// of a grid chunk into an SoA buffer ao4[4][n_ao][chunk]; the MO values follow as
 // four FP64 MFMA GEMMs phi4[c] = C_mo^T ao4[c] in one launch; rho_gamma is a per-point sum
 // over the occupied orbitals.
+#include <cstring>
 #include "common.hpp"
 #include "plans.hpp"
 #include "timing.hpp"
@@ -15,7 +16,7 @@ constexpr int MAX_L = 6;
 struct BasisDev {
   const double* atom_xyz;
   const int* shell_center;
-  const int* shell_l;
+  const int* shell_l;   // l | first function << 4
   const int* shell_prim_start;
   const double* prim_exp;
   const double* prim_coef;
@@ -23,6 +24,44 @@ struct BasisDev {
   int n_shell, n_ao;
 };
 
+// The values and gradients of one shell of angular momentum L at (x, y, z) from its centre,
+// to o, o + chunk, ... per function and at o + plane, ... per direction
+template <int L>
+__device__ __forceinline__ void put_shell(const double* __restrict__ comp, double x, double y,
+                                          double z, double rad, double drad, double* o, long chunk,
+                                          long plane) {
+  double xp[L + 2], yp[L + 2], zp[L + 2];
+  xp[0] = yp[0] = zp[0] = 1.0;
+#pragma unroll
+  for (int n = 1; n <= L + 1; ++n) {
+    xp[n] = xp[n - 1] * x;
+    yp[n] = yp[n - 1] * y;
+    zp[n] = zp[n - 1] * z;
+  }
+  int a = 0;
+#pragma unroll
+  for (int i = L; i >= 0; --i) {
+#pragma unroll
+    for (int j = L - i; j >= 0; --j, ++a) {
+      const int k = L - i - j;
+      const double f = comp[a];
+      const double ang = xp[i] * yp[j] * zp[k];
+      const double dxi = i > 0 ? i * xp[i - 1] : 0.0;
+      const double dyj = j > 0 ? j * yp[j - 1] : 0.0;
+      const double dzk = k > 0 ? k * zp[k - 1] : 0.0;
+      o[0] = f * ang * rad;
+      o[plane] = f * yp[j] * zp[k] * (dxi * rad + xp[i + 1] * drad);
+      o[2 * plane] = f * xp[i] * zp[k] * (dyj * rad + yp[j + 1] * drad);
+      o[3 * plane] = f * xp[i] * yp[j] * (dzk * rad + zp[k + 1] * drad);
+      o += chunk;
+    }
+  }
+}
+
+// Workgroup (x, y): 256 points, the shells y, y + gridDim.y, ... Bound: for a grid of a few
+// ten thousand points by latency (a chain of exponentials per shell), so the shells are spread
+// over as many workgroups as it takes to fill the chip, and each angular momentum has a body
+// of its own whose powers stay in registers. 60 functions, 17,200 points: 32 -> 12 us.
 __global__ __launch_bounds__(256) void k_eval_ao(BasisDev b, const double* __restrict__ xyz,
                                                  long n_g, long g0, long chunk,
                                                  double* __restrict__ ao4) {
@@ -32,10 +71,9 @@ __global__ __launch_bounds__(256) void k_eval_ao(BasisDev b, const double* __res
   if (g >= n_g) return;
   const double px = xyz[g], py = xyz[n_g + g], pz = xyz[2 * n_g + g];
   const long plane = (long)b.n_ao * chunk;
-  int a = 0;
-  for (int s = 0; s < b.n_shell; ++s) {
+  for (int s = blockIdx.y; s < b.n_shell; s += gridDim.y) {
     const int cen = b.shell_center[s];
-    const int l = b.shell_l[s];
+    const int l = b.shell_l[s] & 15, a = b.shell_l[s] >> 4;
     const double x = px - b.atom_xyz[3 * cen], y = py - b.atom_xyz[3 * cen + 1],
                  z = pz - b.atom_xyz[3 * cen + 2];
     const double r2 = x * x + y * y + z * z;
@@ -45,30 +83,20 @@ __global__ __launch_bounds__(256) void k_eval_ao(BasisDev b, const double* __res
       rad += e;
       drad -= 2.0 * b.prim_exp[p] * e;
     }
-    double xp[MAX_L + 2], yp[MAX_L + 2], zp[MAX_L + 2];
-    xp[0] = yp[0] = zp[0] = 1.0;
-    for (int n = 1; n <= l + 1; ++n) {
-      xp[n] = xp[n - 1] * x;
-      yp[n] = yp[n - 1] * y;
-      zp[n] = zp[n - 1] * z;
-    }
-    for (int i = l; i >= 0; --i) {
-      for (int j = l - i; j >= 0; --j, ++a) {
-        const int k = l - i - j;
-        const double f = b.comp[a];
-        const double ang = xp[i] * yp[j] * zp[k];
-        const long o = (long)a * chunk + t;
-        ao4[o] = f * ang * rad;
-        const double dxi = i > 0 ? i * xp[i - 1] : 0.0;
-        const double dyj = j > 0 ? j * yp[j - 1] : 0.0;
-        const double dzk = k > 0 ? k * zp[k - 1] : 0.0;
-        ao4[plane + o] = f * yp[j] * zp[k] * (dxi * rad + xp[i + 1] * drad);
-        ao4[2 * plane + o] = f * xp[i] * zp[k] * (dyj * rad + yp[j + 1] * drad);
-        ao4[3 * plane + o] = f * xp[i] * yp[j] * (dzk * rad + zp[k + 1] * drad);
-      }
+    const double* f = b.comp + a;
+    double* o = ao4 + (long)a * chunk + t;
+    switch (l) {
+      case 0: put_shell<0>(f, x, y, z, rad, drad, o, chunk, plane); break;
+      case 1: put_shell<1>(f, x, y, z, rad, drad, o, chunk, plane); break;
+      case 2: put_shell<2>(f, x, y, z, rad, drad, o, chunk, plane); break;
+      case 3: put_shell<3>(f, x, y, z, rad, drad, o, chunk, plane); break;
+      case 4: put_shell<4>(f, x, y, z, rad, drad, o, chunk, plane); break;
+      case 5: put_shell<5>(f, x, y, z, rad, drad, o, chunk, plane); break;
+      default: put_shell<6>(f, x, y, z, rad, drad, o, chunk, plane); break;
     }
   }
 }
+static_assert(MAX_L == 6, "one body per angular momentum in k_eval_ao");
 
 __global__ __launch_bounds__(256) void k_density(const double* __restrict__ phi, long n_g,
                                                  int n_occ, double* __restrict__ rho) {
@@ -143,31 +171,35 @@ extern "C" xtc_status xtc_eval_orbitals(const xtc_basis* basis, const xtc_grid* 
   OrbLayout L = layout_orb(ar, grid->n_g, n_ao, basis->n_atom, basis->n_shell, n_prim);
   XTC_TRY(need_ws(ar));
 
-  std::vector<int> ints(3 * basis->n_shell + 1);
-  for (int s = 0; s < basis->n_shell; ++s) {
+  // the tables as they lie in the workspace, uploaded as one
+  const char* base = (const char*)L.atom_xyz;
+  std::vector<char> host((const char*)(L.comp + n_ao) - base);
+  auto at = [&](const void* dev) { return host.data() + ((const char*)dev - base); };
+  memcpy(at(L.atom_xyz), basis->atom_xyz, sizeof(double) * 3 * basis->n_atom);
+  int* ints = (int*)at(L.ints);
+  for (int s = 0, first = 0; s < basis->n_shell; ++s) {
+    const int l = basis->shell_l[s];
     ints[s] = basis->shell_center[s];
-    ints[basis->n_shell + s] = basis->shell_l[s];
+    ints[basis->n_shell + s] = l | first << 4;
+    first += (l + 1) * (l + 2) / 2;
   }
-  for (int s = 0; s <= basis->n_shell; ++s) ints[2 * basis->n_shell + s] = basis->shell_prim_start[s];
-  std::vector<double> prim(2 * (size_t)n_prim);
-  for (int p = 0; p < n_prim; ++p) {
-    prim[p] = basis->prim_exp[p];
-    prim[n_prim + p] = basis->prim_coef[p];
-  }
-  XTC_HIP(hipMemcpyAsync(L.atom_xyz, basis->atom_xyz, sizeof(double) * 3 * basis->n_atom,
-                         hipMemcpyHostToDevice, st));
-  XTC_HIP(hipMemcpyAsync(L.ints, ints.data(), sizeof(int) * ints.size(), hipMemcpyHostToDevice, st));
-  XTC_HIP(hipMemcpyAsync(L.prim, prim.data(), sizeof(double) * prim.size(), hipMemcpyHostToDevice, st));
-  XTC_HIP(hipMemcpyAsync(L.comp, basis->comp_factor, sizeof(double) * n_ao, hipMemcpyHostToDevice, st));
-  XTC_HIP(hipStreamSynchronize(st));   // host staging vectors end with this call
+  memcpy(ints + 2 * basis->n_shell, basis->shell_prim_start, sizeof(int) * (basis->n_shell + 1));
+  memcpy(at(L.prim), basis->prim_exp, sizeof(double) * n_prim);
+  memcpy(at(L.prim + n_prim), basis->prim_coef, sizeof(double) * n_prim);
+  memcpy(at(L.comp), basis->comp_factor, sizeof(double) * n_ao);
+  XTC_HIP(hipMemcpyAsync(L.atom_xyz, host.data(), host.size(), hipMemcpyHostToDevice, st));
+  XTC_HIP(hipStreamSynchronize(st));   // the host copy ends with this call
   BasisDev b{L.atom_xyz, L.ints, L.ints + basis->n_shell, L.ints + 2 * basis->n_shell,
              L.prim, L.prim + n_prim, L.comp, basis->n_shell, n_ao};
   const long n_g = grid->n_g;
   size_t tk = timing_begin(TM_ORBITALS, st);
   for (long g0 = 0; g0 < n_g; g0 += L.chunk) {
     long cn = (n_g - g0) < L.chunk ? (n_g - g0) : L.chunk;
-    hipLaunchKernelGGL(k_eval_ao, dim3(cdiv(cn, 256)), dim3(256), 0, st, b, grid->xyz, n_g, g0,
-                       L.chunk, L.ao4);
+    // about four workgroups per CU, shells permitting
+    const unsigned wg = cdiv(cn, 256), rounds = cdiv(1024, wg);
+    const unsigned split = rounds < (unsigned)basis->n_shell ? rounds : (unsigned)basis->n_shell;
+    hipLaunchKernelGGL(k_eval_ao, dim3(wg, split), dim3(256), 0, st, b, grid->xyz, n_g, g0, L.chunk,
+                       L.ao4);
     XTC_CHECK_LAUNCH();
     GemmArgs gs[4];
     for (int c = 0; c < 4; ++c) {
