@@ -6,7 +6,7 @@
 //             panel and trailing updates are GEMMs; on a non-positive pivot the
 //             adaptive Tikhonov retry re-factors A + shift_k I
 //   RHS       per grid chunk: P = Phi_mu^T Phi, B = P o P or (dPhi_mu^T dPhi)_c o P
-//   solves    blocked forward and backward substitution as GEMMs with the
+//   solves    forward and backward substitution, a launch each (solve.hip), with the
 //             inverted diagonal blocks; the weighted residual
 //             sum_g w^2 (|m_g|^2 - |L^{-1} B(g)|^2) falls out of the forward solve.
 // The fit is column-separable in g, so the grid is processed in chunks and the

@@ -15,7 +15,7 @@
 //      an FP32 medium sum over the launch, FP64 in the panel, scales removed exactly.
 // The A operand and its per-row exponents are the split operand of the EE path. The FP64
 // path of the BH form takes its pair values from k_bh_pairs_f64 below (the same tables and
-// sums, the values stored unscaled in FP64 for k_stage1_f64_pv).
+// sums, the values stored unscaled in FP64 for k_stage1_products).
 #include <algorithm>
 #include <type_traits>
 #include "bh.hpp"
@@ -345,7 +345,7 @@ __global__ __launch_bounds__(256, 2) void k_bh_pairs(
 }
 
 // The FP64 path's pair values (the BH form): the same tables and nuclear sums as k_bh_pairs,
-// the four channels stored unscaled in FP64 for k_stage1_f64_pv, per 16-ket step s of the
+// the four channels stored unscaled in FP64 for k_stage1_products, per 16-ket step s of the
 // launch and 64-bra tile t: pv64[t][s][q][c][gk][gb] for the pair (bra gb, ket 4 gk + q).
 // The grid covers whole 64-bra tiles (two 32-bra halves; bras past the range repeat its
 // last point).
