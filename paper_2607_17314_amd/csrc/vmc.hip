@@ -1123,27 +1123,29 @@ __global__ __launch_bounds__(VMC_GN_THREADS) void k_vmc_gn(const double* __restr
       v += (dclip(e, d, ccol) - sh.mdt[ccol]) * ((e < lo ? lo : (e > hi ? hi : e)) - mean);
     });
     if (t < nth) sh.grad[t] = 2.0 * a1 / (double)(N - 1);
-    // C by blocks of 4 x 4 entries (p, q), p's block not above q's, up to GN_BLK a thread; the
-    // walkers' dr rows (ld doubles, zeros past nth) pass through two buffers in the space that
-    // C takes at the end, the next tile loaded while the current one multiplies.
-    const int nq = (nth + 3) / 4, ld = 4 * nq, nblk = nq * (nq + 1) / 2;
+    // C by blocks of 16 x 16 entries (p, q), p's block not above q's, up to GN_BLK a wave, on
+    // the FP64 matrix cores: four walkers a step, added in turn as fused multiply-adds
+    // (measured, bit for bit). The walkers' dr rows (ld doubles, zeros past nth and past the
+    // last walker) pass through two buffers in the space that C takes at the end, the next
+    // tile loaded while the current one multiplies.
+    typedef double d4 __attribute__((ext_vector_type(4)));
+    const int nb = (nth + 15) / 16, nblk = nb * (nb + 1) / 2;
+    const int ld = 16 * (nb | 1);   // an odd number of 16s: two rows fill the 64 banks
     constexpr int HALF = VMC_MAX_THETA * VMC_MAX_THETA / 2, GN_LOADS = HALF / VMC_GN_THREADS;
-    constexpr int MAXQ4 = VMC_MAX_THETA / 4;
-    constexpr int GN_BLK = (MAXQ4 * (MAXQ4 + 1) / 2 + VMC_GN_THREADS - 1) / VMC_GN_THREADS;
-    const int tl = HALF / ld;   // walkers of a tile
-    double cacc[GN_BLK][4][4];
-    int cp[GN_BLK], cq[GN_BLK];   // first row and column of this thread's blocks
+    constexpr int WAVES = VMC_GN_THREADS / 64, MAXB = VMC_MAX_THETA / 16;
+    constexpr int GN_BLK = (MAXB * (MAXB + 1) / 2 + WAVES - 1) / WAVES;
+    const int tl = HALF / ld & ~3;   // walkers of a tile
+    const int wave = __builtin_amdgcn_readfirstlane(t >> 6), li = t & 15, lk = (t >> 4) & 3;
+    d4 cacc[GN_BLK];
+    int cp[GN_BLK], cq[GN_BLK];   // first row and column of this wave's blocks
 #pragma unroll
     for (int u = 0; u < GN_BLK; ++u) {
-      int x = t + u * VMC_GN_THREADS, p = 0;
+      int x = wave + u * WAVES, p = 0;
       if (x >= nblk) x = 0;
       while (x > p) x -= ++p;
-      cp[u] = 4 * p;
-      cq[u] = 4 * x;
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) cacc[u][i][j] = 0.0;
+      cp[u] = 16 * p;
+      cq[u] = 16 * x;
+      cacc[u] = (d4){0.0, 0.0, 0.0, 0.0};
     }
     double ev[GN_LOADS], dv[GN_LOADS];
     const int k_step = VMC_GN_THREADS / ld, p_step = VMC_GN_THREADS % ld;
@@ -1173,45 +1175,34 @@ __global__ __launch_bounds__(VMC_GN_THREADS) void k_vmc_gn(const double* __restr
     for (long k0 = 0; k0 < N; k0 += tl, buf ^= 1) {
       double* tile = sh.C + buf * HALF;
       each([&](int i, int kk, int p) {
-        if (kk < tl) tile[kk * ld + p] = p < nth ? dclip(ev[i], dv[i], p) - sh.mdt[p] : 0.0;
+        if (kk < tl)
+          tile[kk * ld + p] = p < nth && k0 + kk < N ? dclip(ev[i], dv[i], p) - sh.mdt[p] : 0.0;
       });
       if (k0 + tl < N) load(k0 + tl);
       __syncthreads();   // the tile before this one is read to the end
       const int nk = (int)(N - k0 < tl ? N - k0 : tl);
 #pragma unroll
       for (int u = 0; u < GN_BLK; ++u)
-        if (t + u * VMC_GN_THREADS < nblk) {
-          const double* rp = tile + cp[u];
-          const double* rq = tile + cq[u];
+        if (wave + u * WAVES < nblk) {
+          const double* rp = tile + lk * ld + li + cp[u];
+          const double* rq = tile + lk * ld + li + cq[u];
 #pragma unroll 4
-          for (int kk = 0; kk < nk; ++kk) {
-            double vp[4], vq[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-              vp[i] = rp[kk * ld + i];
-              vq[i] = rq[kk * ld + i];
-            }
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-              for (int j = 0; j < 4; ++j) cacc[u][i][j] += vp[i] * vq[j];
-          }
+          for (int kk = 0; kk < nk; kk += 4)
+            cacc[u] = __builtin_amdgcn_mfma_f64_16x16x4f64(rp[kk * ld], rq[kk * ld], cacc[u], 0, 0, 0);
         }
     }
     __syncthreads();   // the tile space becomes C
 #pragma unroll
     for (int u = 0; u < GN_BLK; ++u)
-      if (t + u * VMC_GN_THREADS < nblk) {
+      if (wave + u * WAVES < nblk) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            const int pp = cp[u] + i, qq = cq[u] + j;
-            if (qq > pp || pp >= nth) continue;
-            const double c = cacc[u][i][j] * inv_n + (pp == qq ? lam : 0.0);
-            sh.C[pp * nth + qq] = c;
-            sh.C[qq * nth + pp] = c;
-          }
+        for (int r = 0; r < 4; ++r) {
+          const int pp = cp[u] + lk + 4 * r, qq = cq[u] + li;
+          if (qq > pp || pp >= nth) continue;
+          const double c = cacc[u][r] * inv_n + (pp == qq ? lam : 0.0);
+          sh.C[pp * nth + qq] = c;
+          sh.C[qq * nth + pp] = c;
+        }
       }
   }
   __syncthreads();
