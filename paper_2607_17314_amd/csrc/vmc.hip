@@ -954,8 +954,8 @@ __global__ __launch_bounds__(64) void k_vmc_energy_bh(VmcDev v, VmcBH bh_in,
 // a tree or the segments in turn; an entry of C above GN_FEW parameters over all walkers in
 // turn. Bound: the latency of one workgroup, so above GN_FEW parameters the loads go out in
 // runs ahead of the sums, and the factorisation has a thread per row. 50 parameters of 8,192
-// walkers 2,725 -> 1,315 us, 128 of 8,192 23.0 -> 3.5 ms (against tiles loaded between two
-// barriers, one row of four entries per thread and step, the factorisation on one thread).
+// walkers 2,725 -> 1,031 us, 128 of 8,192 23.0 -> 2.7 ms (against tiles loaded between two
+// barriers, one row of four entries of C per thread and step, the factorisation on one thread).
 struct GnShared {
   double red[VMC_GN_THREADS];
   double dm[VMC_MAX_THETA], dmad[VMC_MAX_THETA], mdt[VMC_MAX_THETA], grad[VMC_MAX_THETA];
@@ -1074,24 +1074,29 @@ __global__ __launch_bounds__(VMC_GN_THREADS) void k_vmc_gn(const double* __restr
                        ? VMC_MAX_THETA * VMC_MAX_THETA / nth : VMC_GN_THREADS;
     const int S = VMC_GN_THREADS / nth, ccol = t % nth, cseg = t / nth;
     auto colsum = [&](auto f) {   // the column total of f(sum, e, dE) on threads t < nth
-      constexpr int U = 16;
+      constexpr int U = 32;
       double v = 0.0;
       int kk = cseg;
-      for (long k0 = 0; cseg < S && k0 < N;) {
+      long k = cseg;
+      const double* pe = E + cseg;
+      const double* pd = dE + (long)cseg * nth + ccol;
+      while (cseg < S && k < N) {
         double e[U], d[U];
         bool in[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-          const long k = k0 + kk;
+        for (int u = 0; u < U; ++u) {   // past the last walker: the first, not added
           in[u] = k < N;
-          const long kc = in[u] ? k : N - 1;
-          e[u] = E[kc];
-          d[u] = dE[kc * nth + ccol];
+          e[u] = *(in[u] ? pe : E);
+          d[u] = *(in[u] ? pd : dE);
+          int next = S;
           kk += S;
-          if (kk >= tk) {
+          if (kk >= tk) {   // the next tile's walker cseg
+            next = tk + cseg - (kk - S);
             kk = cseg;
-            k0 += tk;
           }
+          k += next;
+          pe += next;
+          pd += next * nth;
         }
 #pragma unroll
         for (int u = 0; u < U; ++u)
