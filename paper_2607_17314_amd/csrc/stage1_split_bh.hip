@@ -70,48 +70,55 @@ static void bh_split_exponents(const BHTable& T, const EECoef& cf, int* eg, int*
 // (4 banks) apart modulo the 64 banks, instead of all in one bank.
 __host__ __device__ constexpr int bh_ket_stride(int nn) { return nn * BH_NO * BH_NP + 2; }
 
-// LDS tables of the pair-value kernels, in doubles: bra tables [nn][a, grad a][32 bras], two
-// ket tables [16 kets][bh_ket_stride(nn)], two tables a_I [nn][16 kets], csym [t][m][n][o],
-// nuclei [BH_MAXNUC][x, y, z, b]
-__host__ __device__ constexpr long bh_tables_lds_doubles(int nn) {
-  return (long)nn * 4 * SB + 2 * 16L * bh_ket_stride(nn) + 2 * 16L * nn +
-         BH_MAXTYPE * BH_NP * BH_NP * BH_NO + 4L * BH_MAXNUC;
+// LDS tables of the pair-value kernels, in doubles: bra tables [nn][a, grad a][32 bras], one
+// ket table [16 kets][bh_ket_stride(nn)] (two: 1 + ahead), as many tables a_I [nn][16 kets],
+// csym [t][m][n][o]
+__host__ __device__ constexpr long bh_tables_lds_doubles(int nn, int ahead) {
+  return (long)nn * 4 * SB + (1 + ahead) * (16L * bh_ket_stride(nn) + 16L * nn) +
+         BH_MAXTYPE * BH_NP * BH_NP * BH_NO;
 }
 
 // LDS of k_bh_pairs: the tables, then the staged half-precision fragments (two k-steps'
 // worth, 2 x 4096 halves)
-__host__ __device__ constexpr long bh_pairs_lds_doubles(int nn) {
-  return bh_tables_lds_doubles(nn) + 2 * 4096 / 4;
+__host__ __device__ constexpr long bh_pairs_lds_doubles(int nn, int ahead) {
+  return bh_tables_lds_doubles(nn, ahead) + 2 * 4096 / 4;
+}
+
+// Whether a workgroup keeps the next step's ket tables beside the current one's: yes, unless
+// that costs the second workgroup of the CU (160 KB of LDS), from 12 to 20 nuclei. 20 nuclei,
+// 194,000 points, per launch of 16,384 x 16,384 pairs: 19.8 ms with them, 14.1 without.
+static int bh_tables_ahead(int nn) {
+  const long half = 160 * 1024 / 2 / (long)sizeof(double);
+  return bh_pairs_lds_doubles(nn, 1) <= half || bh_pairs_lds_doubles(nn, 0) > half ? 1 : 0;
 }
 
 struct BHLds {
   double (*TB)[4][SB];   // bra tables of the 32-bra tile
-  double* TK;            // ket tables of 16-ket steps, even, then odd
+  double* TK;            // ket tables of 16-ket steps (ahead: even, then odd)
   double* AT;            // their a_I
   double* CS;            // csym
-  double (*NU)[4];       // nuclei
   int ks;                // doubles per ket in TK
+  int ahead;             // the next step's tables are kept beside the current one's
 };
 
-__device__ __forceinline__ BHLds bh_lds(double* sm, int nn) {
+__device__ __forceinline__ BHLds bh_lds(double* sm, int nn, int ahead) {
   BHLds L;
   L.TB = (double(*)[4][SB])sm;
   L.ks = bh_ket_stride(nn);
   L.TK = sm + nn * 4 * SB;
-  L.AT = L.TK + 2 * 16 * L.ks;
-  L.CS = L.AT + 2 * 16 * nn;
-  L.NU = (double(*)[4])(L.CS + BH_MAXTYPE * BH_NP * BH_NP * BH_NO);
+  L.AT = L.TK + (1 + ahead) * 16 * L.ks;
+  L.CS = L.AT + (1 + ahead) * 16 * nn;
+  L.ahead = ahead;
   return L;
 }
 
-// csym, the nuclei and the bra tables of bra tile bt (bras past the range repeat its last
+// csym and the bra tables of bra tile bt (bras past the range repeat its last
 // point); followed by a barrier before any use
 __device__ __forceinline__ void bh_fill_bra_tables(const BHLds& L, const BHTable* __restrict__ T,
                                                    const double* __restrict__ xyz, long n_g,
                                                    long b0, long bn, long bt, int nn, int tid) {
   for (int e = tid; e < BH_MAXTYPE * BH_NP * BH_NP * BH_NO; e += 256)
     L.CS[e] = (&T->csym[0][0][0][0])[e];
-  for (int e = tid; e < 4 * nn; e += 256) L.NU[e / 4][e % 4] = T->nuc[e / 4][e % 4];
   const long blast = b0 + bn - 1;
   for (int e = tid; e < nn * SB; e += 256) {
     const int I = e / SB, bb = e % SB;
@@ -126,12 +133,12 @@ __device__ __forceinline__ void bh_fill_bra_tables(const BHLds& L, const BHTable
 }
 
 // a_I of ket tid % 16 of a step at (x, y, z), nuclei tid / 16, tid / 16 + 16
-__device__ __forceinline__ void bh_ket_a(const BHLds& L, double* AT, double x, double y, double z,
-                                         int nn, int tid) {
+__device__ __forceinline__ void bh_ket_a(const BHTable* __restrict__ T, double* AT, double x,
+                                         double y, double z, int nn, int tid) {
   for (int I = tid >> 4; I < nn; I += 16) {
-    const double dx = x - L.NU[I][0], dy = y - L.NU[I][1], dz = z - L.NU[I][2];
+    const double dx = x - T->nuc[I][0], dy = y - T->nuc[I][1], dz = z - T->nuc[I][2];
     const double r = sqrt(dx * dx + dy * dy + dz * dz);
-    AT[I * 16 + (tid & 15)] = L.NU[I][3] * r / (1.0 + L.NU[I][3] * r);
+    AT[I * 16 + (tid & 15)] = T->nuc[I][3] * r / (1.0 + T->nuc[I][3] * r);
   }
 }
 
@@ -159,10 +166,11 @@ __device__ __forceinline__ void bh_ket_gamma(const BHLds& L, const double* AT, d
 }
 
 // The 16-ket steps of a workgroup from ket kbeg (kets past the grid repeat its last point):
-// pairs(step) with its ket tables in half step & 1 of L.TK. While a step's pairs are made, the
-// gammas of the next step and the a_I of the one after it go to the other tables, so that a
-// step has one barrier and nothing to wait for behind it. top(step) comes first in a step,
-// for loads and for stores of what the step before left in LDS.
+// pairs(step) with its ket tables in half step & ahead of L.TK. Ahead: while a step's pairs are
+// made, the gammas of the next step and the a_I of the one after it go to the other tables, so
+// that a step has one barrier and nothing to wait for behind it. Else the a_I alone are made a
+// step ahead, and the gammas between two barriers. top(step) comes first in a step, for loads
+// and for stores of what the step before left in LDS.
 template <class Top, class Pairs>
 __device__ __forceinline__ void bh_ket_steps(const BHLds& L, const BHTable* __restrict__ T,
                                              const double* __restrict__ xyz, long n_g, long kbeg,
@@ -176,23 +184,31 @@ __device__ __forceinline__ void bh_ket_steps(const BHLds& L, const BHTable* __re
     y = xyz[n_g + g];
     z = xyz[2 * n_g + g];
   };
+  const int ahead = L.ahead;
   double x, y, z;
-  __syncthreads();   // the nuclei, csym and bra tables are in
-  for (int i = 0; i < 2; ++i) {
+  __syncthreads();   // csym and the bra tables are in
+  for (int i = 0; i <= ahead; ++i) {
     ket(i, x, y, z);
-    bh_ket_a(L, L.AT + i * 16 * nn, x, y, z, nn, tid);
+    bh_ket_a(T, L.AT + i * 16 * nn, x, y, z, nn, tid);
   }
-  XTC_LDS_DONE();
-  __syncthreads();
-  bh_ket_gamma(L, L.AT, L.TK, nn, types, tid);
-  for (int s = 0; s < nsteps; ++s) {
+  if (ahead) {
     XTC_LDS_DONE();
     __syncthreads();
-    ket(s + 2, x, y, z);
+    bh_ket_gamma(L, L.AT, L.TK, nn, types, tid);
+  }
+  for (int s = 0; s < nsteps; ++s) {
+    const int odd = (s + ahead) & ahead;   // the half of the step whose gammas are made now
+    XTC_LDS_DONE();
+    __syncthreads();
+    ket(s + 1 + ahead, x, y, z);
     top(s);
-    bh_ket_gamma(L, L.AT + ((s + 1) & 1) * 16 * nn, L.TK + ((s + 1) & 1) * 16 * L.ks, nn, types, tid);
+    bh_ket_gamma(L, L.AT + odd * 16 * nn, L.TK + odd * 16 * L.ks, nn, types, tid);
+    if (!ahead) {
+      XTC_LDS_DONE();
+      __syncthreads();
+    }
     pairs(s);
-    bh_ket_a(L, L.AT + (s & 1) * 16 * nn, x, y, z, nn, tid);
+    bh_ket_a(T, L.AT + (s & ahead) * 16 * nn, x, y, z, nn, tid);
   }
   XTC_LDS_DONE();
   __syncthreads();
@@ -241,11 +257,11 @@ __global__ __launch_bounds__(256, 2) void k_bh_pairs(
     const double* __restrict__ xyz, const double* __restrict__ w, const double* __restrict__ rho,
     const double* __restrict__ rhot, long n_g, long b0, long bn, long c0, long nloc, EECoef cf,
     const BHTable* __restrict__ T, int eg, int es, h8* __restrict__ pv,
-    double* __restrict__ part, long bp, int first) {
+    double* __restrict__ part, long bp, int first, int ahead) {
   extern __shared__ double sm[];
   const int nn = T->n_nuc;
-  const BHLds L = bh_lds(sm, nn);
-  h8* ST = (h8*)(sm + bh_tables_lds_doubles(nn));   // [2][512] h8
+  const BHLds L = bh_lds(sm, nn, ahead);
+  h8* ST = (h8*)(sm + bh_tables_lds_doubles(nn, ahead));   // [2][512] h8
   _Float16* STh = (_Float16*)ST;
   const int tid = threadIdx.x, kk = tid & 15, q2 = tid >> 4;
   const long bt = blockIdx.x;
@@ -284,7 +300,7 @@ __global__ __launch_bounds__(256, 2) void k_bh_pairs(
   auto pairs = [&](int t) {
     unsigned pk[2][4];   // per bra and channel: (hi, lo) halves of the scaled value
     double F[2][BH_NO], GF[2][BH_NO][3];
-    bh_two_pairs(L, L.TK + (t & 1) * 16 * L.ks, nn, q2, kk, F, GF);
+    bh_two_pairs(L, L.TK + (t & L.ahead) * 16 * L.ks, nn, q2, kk, F, GF);
 #pragma unroll
     for (int v = 0; v < 2; ++v) {
       double o[4];
@@ -352,10 +368,10 @@ __global__ __launch_bounds__(256, 2) void k_bh_pairs(
 __global__ __launch_bounds__(256, 2) void k_bh_pairs_f64(const double* __restrict__ xyz, long n_g,
                                                       long b0, long bn, long c0, long nloc,
                                                       EECoef cf, const BHTable* __restrict__ T,
-                                                      double* __restrict__ pv64) {
+                                                      double* __restrict__ pv64, int ahead) {
   extern __shared__ double sm[];
   const int nn = T->n_nuc;
-  const BHLds L = bh_lds(sm, nn);
+  const BHLds L = bh_lds(sm, nn, ahead);
   const int tid = threadIdx.x, kk = tid & 15, q2 = tid >> 4;
   const long bt = blockIdx.x;
   const long blast = b0 + bn - 1;
@@ -386,7 +402,7 @@ __global__ __launch_bounds__(256, 2) void k_bh_pairs_f64(const double* __restric
   };
   auto pairs = [&](int t) {
     double F[2][BH_NO], GF[2][BH_NO][3];
-    bh_two_pairs(L, L.TK + (t & 1) * 16 * L.ks, nn, q2, kk, F, GF);
+    bh_two_pairs(L, L.TK + (t & L.ahead) * 16 * L.ks, nn, q2, kk, F, GF);
     double* d = dst + (cl0 * 8 + t) * 4096;
 #pragma unroll
     for (int v = 0; v < 2; ++v) {
@@ -408,9 +424,10 @@ xtc_status bh_pair_values_f64(const Stage1Args& a, const EECoef& cf, long c0, lo
   XTC_REQUIRE(a.bh && a.bh_host && a.pv64, "FP64 BH stage 1: no correlator table or buffer");
   XTC_REQUIRE(nloc >= 1 && nloc <= SMED && a.bn <= a.bp, "FP64 BH stage 1: bad launch range");
   const int nn = a.bh_host->n_nuc;
-  const size_t lds = sizeof(double) * (size_t)bh_tables_lds_doubles(nn);
+  const int ahead = bh_tables_ahead(nn);
+  const size_t lds = sizeof(double) * (size_t)bh_tables_lds_doubles(nn, ahead);
   hipLaunchKernelGGL(k_bh_pairs_f64, dim3(2 * cdiv(a.bn, 64), cdiv(nloc, GCH)), dim3(256), lds, st,
-                     a.xyz, a.n_g, a.b0, a.bn, c0, nloc, cf, a.bh, a.pv64);
+                     a.xyz, a.n_g, a.b0, a.bn, c0, nloc, cf, a.bh, a.pv64, ahead);
   XTC_CHECK_LAUNCH();
   return XTC_OK;
 }
@@ -596,7 +613,8 @@ xtc_status stage1_split_bh(const Stage1Args& a, const EECoef& cf, void* scratch,
   int eg = 0, es = 0;
   bh_split_exponents(*a.bh_host, cf, &eg, &es);
   const int nn = a.bh_host->n_nuc;
-  const size_t lds_gen = sizeof(double) * (size_t)std::max(bh_pairs_lds_doubles(nn), 8L * SB * 16);
+  const int ahead = bh_tables_ahead(nn);
+  const size_t lds_gen = sizeof(double) * (size_t)std::max(bh_pairs_lds_doubles(nn, ahead), 8L * SB * 16);
   const size_t lds_pv = sizeof(h8) * 2 * PV_CHUNK;
   const int nrt = (int)(S.rows_pad / SR);
   const long nchunks = S.n_g_pad / SKC;
@@ -611,7 +629,7 @@ xtc_status stage1_split_bh(const Stage1Args& a, const EECoef& cf, void* scratch,
     size_t tk = timing_begin(TM_S1_PAIRS, st);
     hipLaunchKernelGGL(k_bh_pairs, dim3(nbt, cdiv(nloc, GCH)), dim3(256), lds_gen, st, a.xyz, a.w,
                        a.rho, a.rhot, a.n_g, a.b0, a.bn, c0, nloc, cf, a.bh, eg, es, pv, part,
-                       a.bp, c0 == 0 ? 1 : 0);
+                       a.bp, c0 == 0 ? 1 : 0, ahead);
     timing_end(tk, st);
     XTC_CHECK_LAUNCH();
     tk = timing_begin(TM_S1_KERNEL, st);
