@@ -11,14 +11,10 @@
 // where U_ee = sum_o cee_o rbar^o collects the (0, 0, o) terms (each carries a factor 2
 // per nucleus). At r12 = 0 the rhat12 part is dropped and |grad u|^2 = |N|^2 + S^2.
 #pragma once
+#include "bh_lds.hpp"
 #include "contract.hpp"
 
 namespace xtc {
-
-constexpr int BH_MAXNUC = 24;   // nuclei
-constexpr int BH_MAXTYPE = 2;   // nucleus types
-constexpr int BH_NP = 4;        // powers 0..3 of a_iI in the nuclear terms
-constexpr int BH_NO = 4;        // powers 0..3 of rbar12 in the nuclear terms
 
 struct BHTable {
   int n_nuc;

@@ -66,31 +66,7 @@ static void bh_split_exponents(const BHTable& T, const EECoef& cf, int* eg, int*
   *es = 14 - 2 * ex;
 }
 
-// Doubles per ket in the LDS ket tables: the 16 kets of a wave read at once sit 2 doubles
-// (4 banks) apart modulo the 64 banks, instead of all in one bank.
-__host__ __device__ constexpr int bh_ket_stride(int nn) { return nn * BH_NO * BH_NP + 2; }
-
-// LDS tables of the pair-value kernels, in doubles: bra tables [nn][a, grad a][32 bras], one
-// ket table [16 kets][bh_ket_stride(nn)] (two: 1 + ahead), as many tables a_I [nn][16 kets],
-// csym [t][m][n][o]
-__host__ __device__ constexpr long bh_tables_lds_doubles(int nn, int ahead) {
-  return (long)nn * 4 * SB + (1 + ahead) * (16L * bh_ket_stride(nn) + 16L * nn) +
-         BH_MAXTYPE * BH_NP * BH_NP * BH_NO;
-}
-
-// LDS of k_bh_pairs: the tables, then the staged half-precision fragments (two k-steps'
-// worth, 2 x 4096 halves)
-__host__ __device__ constexpr long bh_pairs_lds_doubles(int nn, int ahead) {
-  return bh_tables_lds_doubles(nn, ahead) + 2 * 4096 / 4;
-}
-
-// Whether a workgroup keeps the next step's ket tables beside the current one's: yes, unless
-// that costs the second workgroup of the CU (160 KB of LDS), from 12 to 20 nuclei. 20 nuclei,
-// 194,000 points, per launch of 16,384 x 16,384 pairs: 19.8 ms with them, 14.1 without.
-static int bh_tables_ahead(int nn) {
-  const long half = 160 * 1024 / 2 / (long)sizeof(double);
-  return bh_pairs_lds_doubles(nn, 1) <= half || bh_pairs_lds_doubles(nn, 0) > half ? 1 : 0;
-}
+static_assert(SB == BH_BRAS, "the LDS tables are laid out for the bra tile");
 
 struct BHLds {
   double (*TB)[4][SB];   // bra tables of the 32-bra tile
@@ -424,7 +400,7 @@ xtc_status bh_pair_values_f64(const Stage1Args& a, const EECoef& cf, long c0, lo
   XTC_REQUIRE(a.bh && a.bh_host && a.pv64, "FP64 BH stage 1: no correlator table or buffer");
   XTC_REQUIRE(nloc >= 1 && nloc <= SMED && a.bn <= a.bp, "FP64 BH stage 1: bad launch range");
   const int nn = a.bh_host->n_nuc;
-  const int ahead = bh_tables_ahead(nn);
+  const int ahead = bh_tables_ahead(BH_PAIRS_F64, nn);
   const size_t lds = sizeof(double) * (size_t)bh_tables_lds_doubles(nn, ahead);
   hipLaunchKernelGGL(k_bh_pairs_f64, dim3(2 * cdiv(a.bn, 64), cdiv(nloc, GCH)), dim3(256), lds, st,
                      a.xyz, a.n_g, a.b0, a.bn, c0, nloc, cf, a.bh, a.pv64, ahead);
@@ -613,8 +589,9 @@ xtc_status stage1_split_bh(const Stage1Args& a, const EECoef& cf, void* scratch,
   int eg = 0, es = 0;
   bh_split_exponents(*a.bh_host, cf, &eg, &es);
   const int nn = a.bh_host->n_nuc;
-  const int ahead = bh_tables_ahead(nn);
-  const size_t lds_gen = sizeof(double) * (size_t)std::max(bh_pairs_lds_doubles(nn, ahead), 8L * SB * 16);
+  const int ahead = bh_tables_ahead(BH_PAIRS, nn);
+  const size_t lds_gen = sizeof(double) * (size_t)std::max(
+      bh_tables_lds_doubles(nn, ahead) + BH_PAIRS.staged, 8L * SB * 16);
   const size_t lds_pv = sizeof(h8) * 2 * PV_CHUNK;
   const int nrt = (int)(S.rows_pad / SR);
   const long nchunks = S.n_g_pad / SKC;
