@@ -15,7 +15,7 @@ __device__ __forceinline__ double horner_fixed(const double (&q)[NQ], double x) 
   return r;
 }
 
-// r = |d| and 1/r (0 and 0 at r = 0) from r2 = |d|^2
+// r = |d| and 1/r (0 and 0 at r = 0, NaN from NaN) from r2 = |d|^2
 __device__ __forceinline__ void sqrt_rsqrt(double r2, double& r, double& rinv) {
   double y = __builtin_amdgcn_rsq(r2);            // ~1/sqrt(r2)
   double g = r2 * y, h = 0.5 * y;                  // g ~ sqrt(r2), h ~ 1/(2 sqrt(r2))
@@ -25,7 +25,7 @@ __device__ __forceinline__ void sqrt_rsqrt(double r2, double& r, double& rinv) {
     g = fma(g, e, g);
     h = fma(h, e, h);
   }
-  const bool zero = !(r2 > 0.0);
+  const bool zero = r2 == 0.0;
   r = zero ? 0.0 : g;
   rinv = zero ? 0.0 : 2.0 * h;
 }

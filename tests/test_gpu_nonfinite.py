@@ -1,0 +1,44 @@
+"""Non-finite inputs are not hidden by the kernels."""
+import numpy as np
+import pytest
+
+from gpu_common import note
+
+pytestmark = pytest.mark.gpu
+
+U1, U3, ULAP, D4, FIELD, ESCALE = 1, 2, 4, 16, 32, 64
+
+
+def _case(n_g, n_mu, powers):
+    from workloads import Correlator, FORM_EE
+    rng = np.random.default_rng(n_g + n_mu)
+    corr = Correlator(FORM_EE, np.array([[0, 0, o] for o in powers], np.int32),
+                      rng.uniform(-0.5, 0.5, (1, len(powers))), 0.9)
+    return (corr, rng.normal(size=(3, n_g)), rng.random(n_g), rng.normal(size=(n_mu, n_g)),
+            rng.random(n_g), rng.choice(n_g, n_mu, replace=False))
+
+
+def _dev(a):
+    import torch
+    return torch.as_tensor(np.ascontiguousarray(a)).cuda()
+
+
+@pytest.mark.parametrize("powers", [[2, 4], [1, 2, 5], [3, 13]])
+@pytest.mark.parametrize("at", [0, 70, 129])
+def test_nan_coordinate_reaches_every_channel(powers, at):
+    """Every sum holds a pair with the point, whose distance is NaN: |grad u|^2 and the
+    Laplacian come out NaN like the gradient channels, and so does the adjoint."""
+    from paper_2607_17314_amd import api
+    corr, xyz, w, xi, rho, piv = _case(130, 9, powers)
+    xyz[1, at] = np.nan
+    grid = api.DeviceGrid.from_host(xyz, w)
+    note(f"NaN coordinate at {at}, powers {powers}")
+    for ch in (U3 | FIELD | ESCALE, U3 | ULAP | FIELD | ESCALE):
+        got = api.kernel_contract(grid, corr, _dev(xi), None, _dev(rho), piv, ch, 0)
+        for k in ("u3", "ulap", "field"):
+            if got[k] is not None:
+                assert bool(got[k].isnan().all()), k
+        assert np.isnan(got["escale"][[0, 3, 4]]).all()
+    cot = {"u3": _dev(np.ones((9, 9)))}
+    dtheta, dd = api.grad(grid, corr, _dev(xi), None, _dev(rho), piv, cot, want_d=True)
+    assert bool(dtheta.isnan().all()) and bool(dd.isnan().all())
