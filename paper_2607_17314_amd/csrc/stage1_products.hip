@@ -44,18 +44,18 @@ struct RowLoader {
     long k = k0 + kf;
     if (!whole && k > n_g - 1) k = n_g - 1;
     wv = w[k];
-    if (!whole && k0 + kf > n_g - 1) wv = 0.0;
+    if (!whole && k0 + kf > n_g - 1) wv = -1.0;   // past the grid: no point's weight
 #pragma unroll
     for (int i = 0; i < N; ++i) v[i] = p[i][k];
   }
-  // kets past the grid have weight zero; 0 * x is stored as zero whatever x is
+  // kets past the grid are stored as zero; 0 * x of a point of weight zero is what it is
   template <int RT>
   __device__ __forceinline__ void store(bool whole, double* lds, int at) {
     keep_vector(at);
 #pragma unroll
     for (int i = 0; i < N; ++i) {
       double x = wv * v[i];
-      if (!whole && wv == 0.0) x = 0.0;
+      if (!whole && wv < 0.0) x = 0.0;
       lds[at + 16 * i] = x;
     }
   }

@@ -42,3 +42,24 @@ def test_nan_coordinate_reaches_every_channel(powers, at):
     cot = {"u3": _dev(np.ones((9, 9)))}
     dtheta, dd = api.grad(grid, corr, _dev(xi), None, _dev(rho), piv, cot, want_d=True)
     assert bool(dtheta.isnan().all()) and bool(dd.isnan().all())
+
+
+@pytest.mark.parametrize("value", [np.inf, np.nan])
+@pytest.mark.parametrize("at", [3, 60, 120, 128, 129])
+def test_nonfinite_vector_at_a_point_of_zero_weight(at, value):
+    """0 * inf and 0 * NaN are NaN in the ket sums of every tile, the first and the last among
+    them; the other vectors are untouched."""
+    from oracle import contract as oc
+    from paper_2607_17314_amd import api
+    corr, xyz, w, xi, rho, piv = _case(130, 9, [2, 4])
+    bra = (32, 56)   # the point is among the kets alone
+    w[at] = 0.0
+    note(f"xi[4] = {value} at point {at} of weight 0")
+    ref = oc.contract(xyz, w, corr, xi, None, rho[piv], rho, U3, bra_range=bra)["u3"]
+    xi[4, at] = value
+    got = api.kernel_contract(api.DeviceGrid.from_host(xyz, w), corr, _dev(xi), None, _dev(rho), piv,
+                              U3, 0, bra=bra)["u3"].cpu().numpy()
+    assert np.isnan(got[:, 4]).all()
+    keep = np.arange(9) != 4
+    # sums of at most 130 x 24 products, each good to a few 1e-16
+    assert np.abs(got[:, keep] - ref[:, keep]).max() < 1e-11 * np.abs(ref).max()
