@@ -74,7 +74,8 @@ __device__ __forceinline__ Cand better(Cand a, Cand b) {
   return a.g <= b.g ? a : b;
 }
 
-// channel: 0 scalar, 1 gradient
+// channel: 0 scalar, 1 gradient. A point whose d is NaN gets the d = 0 that its first factor
+// entry would leave it: the search below compares d's and would lose others to a NaN.
 __global__ __launch_bounds__(PIV_BLOCK) void k_diag(const double* __restrict__ phi4,
                                                     const double* __restrict__ w, long n_g,
                                                     int n_orb, int channel,
@@ -96,7 +97,7 @@ __global__ __launch_bounds__(PIV_BLOCK) void k_diag(const double* __restrict__ p
       }
       dd = w[g] * w[g] * n2 * g2;
     }
-    d[g] = dd;
+    d[g] = dd == dd ? dd : 0.0;
   }
 }
 

@@ -63,3 +63,30 @@ def test_nonfinite_vector_at_a_point_of_zero_weight(at, value):
     keep = np.arange(9) != 4
     # sums of at most 130 x 24 products, each good to a few 1e-16
     assert np.abs(got[:, keep] - ref[:, keep]).max() < 1e-11 * np.abs(ref).max()
+
+
+@pytest.mark.parametrize("at", [0, 4, 6, 255, 256, 699])
+@pytest.mark.parametrize("where", ["value", "gradient"])
+def test_nan_orbital_loses_no_other_point(at, where):
+    """A NaN orbital value or derivative at one point takes that point out of the channels that
+    it enters; the others are selected as without it. The points 5 and 7 carry the largest
+    residuals, next to a NaN."""
+    from oracle import pivots
+    from paper_2607_17314_amd import api
+    rng = np.random.default_rng(at)
+    n_g, n_mu = 700, 40
+    phi4, w = rng.normal(size=(4, 9, n_g)), rng.random(n_g) + 0.1
+    phi4[:, :, 5] *= 3.0
+    phi4[:, :, 7] *= 2.5
+    w[[5, 7]] = 1.1
+    clean = phi4.copy()
+    if where == "value":   # enters both channels
+        phi4[0, 3, at] = np.nan
+        clean[:, :, at] = 0.0
+    else:                  # enters the gradient channel alone
+        phi4[2, 3, at] = np.nan
+        clean[1:, :, at] = 0.0
+    ref = pivots.select_fused(clean, w, n_mu).pivots
+    note(f"NaN orbital {where} at point {at}")
+    got, _, st = api.select_points(_dev(phi4), api.DeviceGrid.from_host(np.zeros((3, n_g)), w), n_mu)
+    assert st == 0 and np.array_equal(got, ref)
