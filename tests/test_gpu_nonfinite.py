@@ -76,8 +76,8 @@ def test_nan_orbital_loses_no_other_point(at, where):
     rng = np.random.default_rng(at)
     n_g, n_mu = 700, 40
     phi4, w = rng.normal(size=(4, 9, n_g)), rng.random(n_g) + 0.1
-    phi4[:, :, 5] *= 3.0
-    phi4[:, :, 7] *= 2.5
+    phi4[:, :, 5] *= 9.0
+    phi4[:, :, 7] *= 5.0
     w[[5, 7]] = 1.1
     clean = phi4.copy()
     if where == "value":   # enters both channels
