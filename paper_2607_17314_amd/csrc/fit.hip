@@ -63,15 +63,17 @@ __global__ __launch_bounds__(256) void k_potrf_diag(double* __restrict__ a, long
   __shared__ double tmp[NB][NB + 1];
   __shared__ double rdiag[NB];
   const int t = threadIdx.x, tx = t & 15, ty = t >> 4;
+  const int blocks = (nb + PB - 1) / PB;   // 16 x 16 blocks a side with rows below nb
   bool bad = false;
-  // rows and columns past nb: unit diagonal
+  // rows and columns past nb: unit diagonal, whose factor and inverse are their own
   for (int e = t; e < NB * NB; e += 256) {
     const int i = e / NB, k = e % NB;
     s[i][k] = (i < nb && k <= i) ? a[(j0 + i) * n + j0 + k] : (i == k ? 1.0 : 0.0);
     sinv[i][k] = 0.0;
   }
+  if (t < NB) rdiag[t] = 1.0;
   __syncthreads();
-  for (int p0 = 0; p0 < NB; p0 += PB) {
+  for (int p0 = 0; p0 < nb; p0 += PB) {
     if (t < NB) {   // wave 0: lane t has row t of the panel
       double c[PB];
 #pragma unroll
@@ -97,7 +99,7 @@ __global__ __launch_bounds__(256) void k_potrf_diag(double* __restrict__ a, long
     __syncthreads();
     // (i, k), p0 + PB <= k <= i, less the panel's products in the order of its columns
     const int r0 = p0 + PB + ty, c0 = p0 + PB + tx;
-    const int left = (NB - p0) / PB - 1;   // 16 x 16 blocks a side
+    const int left = blocks - p0 / PB - 1;
     for (int bi = 0; bi < left; ++bi)
       for (int bk = 0; bk <= bi; ++bk) {
         double x = s[r0 + PB * bi][c0 + PB * bk];
@@ -129,8 +131,8 @@ __global__ __launch_bounds__(256) void k_potrf_diag(double* __restrict__ a, long
     for (int k = 0; k < PB; ++k) v += row[k] * col[k * (NB + 1)];
     return v;
   };
-  for (int d = 1; d < 4; ++d) {
-    for (int J = 0; J + d < 4; ++J) {
+  for (int d = 1; d < blocks; ++d) {
+    for (int J = 0; J + d < blocks; ++J) {
       const int I = J + d;
       const int r = I * PB + ty, c = J * PB + tx;
       double v = 0.0;
@@ -138,7 +140,7 @@ __global__ __launch_bounds__(256) void k_potrf_diag(double* __restrict__ a, long
       tmp[r][c] = v;
     }
     __syncthreads();
-    for (int J = 0; J + d < 4; ++J) {
+    for (int J = 0; J + d < blocks; ++J) {
       const int I = J + d;
       const int r = I * PB + ty, c = J * PB + tx;
       sinv[r][c] = -run(0.0, &sinv[r][I * PB], &tmp[I * PB][c]);
