@@ -13,10 +13,10 @@
 //                    = sum_nu [F(p,r) C(q,s) + C(p,r) F(q,s)],  F = a P + b X,
 // with (P, a, b) = (PK, 1/2, 0) for K, (PU, -1, 1) for dU and (PW = PK/2 + PU, -1, 1) for
 // W = -K + dU: with F formed once by the preparation, a panel is two FP64 MFMA products
-// instead of four. P splits into the projections of the antisymmetric A (PA) and of the
-// symmetric C (PC), each formed for p <= r only. The one-body pieces need only partial
-// traces over the occupied orbitals, formed from the same factors without the four-index
-// tensors.
+// instead of four. In all but small problems P is split into the projections of the
+// antisymmetric A (PA) and of the symmetric C (PC), each formed for p <= r only. The one-body
+// pieces need only partial traces over the occupied orbitals, formed from the same factors
+// without the four-index tensors.
 // Ten atoms (150 orbitals, N_mu 1,500), a panel of 20 orbitals with its preparation:
 // 29.7 -> 10.5 ms (panel 20.7 -> 6.6, 61 TFLOP/s; preparation 9.2 -> 4.7).
 #include "common.hpp"
@@ -26,31 +26,46 @@
 namespace xtc {
 
 struct AsmLayout {
-  double* A3;    // [x, y, z][n_mu][np]: A^c_mu(p,r), pairs p <= r packed
-  double* Cp;    // [n_mu][np]: C_mu(p,r), packed
-  double* C;     // [n_mu][n_orb^2]: C_mu(p,r)
+  bool packed;   // the projections run over the pairs p <= r, else over all
+  double* A3;    // [x, y, z][n_mu][np]: A^c_mu(p,r)
+  double* Cp;    // [n_mu][np]: C_mu(p,r), when packed
+  double* C;     // [n_mu][n_orb^2]: C_mu(p,r); when not packed right behind A3
   double* Xm;    // [n_mu][n_orb^2] = X2 + X3 transposed
-  double* PA; double* PC;  // [n_mu][np]: the projections of A3 and Cp
+  double* PA; double* PC;  // [n_mu][np]: the projections of A3 and Cp, when packed
   double* FK; double* FU; double* FW;   // [n_mu][n_orb^2] each (when requested)
   double* U4;    // [4][n_mu][n_mu] stacked right factors of the projection GEMMs
   double* vec;   // [2][n_mu]: g, phi of the one-body traces
   double* J; double* Kx;   // [n_orb][n_orb] one-body partial traces
   double* dhd;   // [n_orb] diagonal of dh
   long nn;       // n_orb^2
-  long np;       // n_orb (n_orb + 1) / 2
+  long np;       // pairs: n_orb (n_orb + 1) / 2 when packed, else n_orb^2
 };
+
+// Packed pairs halve the projections' work but take two launches more per output (the
+// symmetric part's product and the unpacking): from more 64 x 64 tiles than CUs on. W of one
+// orbital's panel with its preparation, packed and not: 44 orbitals, N_mu 440 (217 tiles) 189,
+// 179 us; 48, 480 (288 tiles) 203, 244 us; 4 orbitals, N_mu 16: 59, 50 us.
+static bool packed_pairs(int n_orb, int n_mu) {
+  return (long)cdiv(n_mu, 64) * cdiv((long)n_orb * n_orb, 64) > 256;
+}
 
 static AsmLayout layout_asm(Arena& ar, int n_orb, int n_mu, uint32_t outputs, bool one_body) {
   AsmLayout L{};
   L.nn = (long)n_orb * n_orb;
-  L.np = (long)n_orb * (n_orb + 1) / 2;
+  L.packed = packed_pairs(n_orb, n_mu);
+  L.np = L.packed ? (long)n_orb * (n_orb + 1) / 2 : L.nn;
   const size_t blk = (size_t)n_mu * L.nn, half = (size_t)n_mu * L.np;
-  L.A3 = ar.take<double>(3 * half);
-  L.Cp = ar.take<double>(half);
-  L.C = ar.take<double>(blk);
+  if (L.packed) {
+    L.A3 = ar.take<double>(3 * half);
+    L.Cp = ar.take<double>(half);
+    L.C = ar.take<double>(blk);
+    L.PA = ar.take<double>(half);
+    L.PC = ar.take<double>(half);
+  } else {
+    L.A3 = ar.take<double>(4 * blk);
+    L.C = L.A3 + 3 * blk;
+  }
   L.Xm = ar.take<double>(blk);
-  L.PA = ar.take<double>(half);
-  L.PC = ar.take<double>(half);
   if (outputs & XTC_ASM_K) L.FK = ar.take<double>(blk);
   if (outputs & XTC_ASM_DU) L.FU = ar.take<double>(blk);
   if (outputs & XTC_ASM_W) L.FW = ar.take<double>(blk);
@@ -81,7 +96,7 @@ __device__ __forceinline__ long packed(int p, int r, int n) {
   return (long)p * n - (long)p * (p - 1) / 2 + (r - p);
 }
 
-// C[mu][p n + r] = C_mu(p,r); for p <= r also Cp and A3[c] = A^c_mu(p,r)
+// C[mu][p n + r] = C_mu(p,r) and A3[c] = A^c_mu(p,r); with Cp packed: A3 and Cp for p <= r
 __global__ void k_pair_factors(const double* __restrict__ phi4, int n, int n_mu, long np,
                                double* __restrict__ A3, double* __restrict__ Cp,
                                double* __restrict__ C) {
@@ -94,9 +109,9 @@ __global__ void k_pair_factors(const double* __restrict__ phi4, int n, int n_mu,
   const long sp = (long)p * n_mu + mu, sr = (long)r * n_mu + mu, comp = (long)n * n_mu;
   const double fp = phi4[sp], fr = phi4[sr];
   C[t] = fp * fr;
-  if (r < p) return;
-  const long o = mu * np + packed(p, r, n);
-  Cp[o] = fp * fr;
+  if (Cp && r < p) return;
+  const long o = Cp ? mu * np + packed(p, r, n) : t;
+  if (Cp) Cp[o] = fp * fr;
 #pragma unroll
   for (int c = 0; c < 3; ++c)
     A3[(long)c * n_mu * np + o] = fp * phi4[(1 + c) * comp + sr] - fr * phi4[(1 + c) * comp + sp];
@@ -217,13 +232,16 @@ static xtc_status prepare(const xtc_assembly* a, uint32_t outputs, const AsmLayo
     XTC_CHECK_LAUNCH();
   }
   const long m2 = (long)n_mu * n_mu;
-  // PA[nu][pr] = sum_{c, mu} U4[c][mu][nu] A3[c][mu][pr], PC likewise from U4[3] and Cp
-  auto project = [&](double* P, const double* B, int seg0, int nseg) {
+  // P[nu][pr] = alpha sum_{seg, mu} U4[seg][mu][nu] B[seg - seg0][mu][pr] + X (or nothing)
+  auto project = [&](double* P, const double* B, int seg0, int nseg, double alpha, const double* X) {
     GemmArgs g{};
     g.M = n_mu; g.N = np; g.K = (long)nseg * n_mu;
     g.A = L.U4 + (long)seg0 * m2; g.a_sm = 1; g.a_sk = n_mu;
     g.B = B; g.b_sk = np; g.b_sn = 1;
     g.C = P; g.c_sm = np; g.c_sn = 1;
+    g.alpha = alpha;
+    g.D = X;
+    g.beta = X ? 1.0 : 0.0;
     return gemm_f64(g, st);
   };
   // U4 from su u1, s3 u3 + sd (D4 + 2 D1), then F = coef (PC + PA) + X
@@ -232,8 +250,12 @@ static xtc_status prepare(const xtc_assembly* a, uint32_t outputs, const AsmLayo
                        sd != 0.0 ? a->D4 : nullptr, sd != 0.0 ? a->D1 : nullptr, n_mu, su, s3, sd,
                        2.0 * sd, L.U4);
     XTC_CHECK_LAUNCH();
-    if (su != 0.0) XTC_TRY(project(L.PA, L.A3, 0, 3));
-    XTC_TRY(project(L.PC, L.Cp, 3, 1));
+    if (!L.packed) {
+      const int seg0 = su != 0.0 ? 0 : 3;   // A3, C or C alone
+      return project(F, L.A3 + (long)seg0 * blk, seg0, 4 - seg0, coef, x ? L.Xm : nullptr);
+    }
+    if (su != 0.0) XTC_TRY(project(L.PA, L.A3, 0, 3, 1.0, nullptr));
+    XTC_TRY(project(L.PC, L.Cp, 3, 1, 1.0, nullptr));
     hipLaunchKernelGGL(k_unpack_f, dim3(cdiv(blk, 256)), dim3(256), 0, st, (const double*)L.PC,
                        su != 0.0 ? (const double*)L.PA : nullptr,
                        x ? (const double*)L.Xm : nullptr, n, n_mu, np, coef, F);
