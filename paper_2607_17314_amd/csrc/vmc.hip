@@ -14,9 +14,11 @@
 // walker tiles staged in LDS for more, all in a fixed order, then a Cholesky solve in
 // LDS.
 #include <cmath>
+#include <type_traits>
 #include "common.hpp"
 #include "plans.hpp"
 #include "timing.hpp"
+#include "vmc_residency.hpp"
 
 namespace xtc {
 
@@ -416,10 +418,12 @@ __device__ __forceinline__ void vmc_ratios(const VmcDev& v, const double* A5, co
 // LDS (doubles): shell centres [n_cent][4], primitives [n_prim][2], A5 [5][n_el][n],
 // aug [n][2n], Ainv [2][n][n], chi [5][n_ao], part [5][64], fac [n], R [n_el][3], red [64];
 // then ints: shell records [n_shell][2], piv.
-// Two waves per SIMD: left alone the compiler takes 274 registers and one wave stays (20 atoms,
-// 16,384 walkers: 2,725 -> 2,441 us, five walkers per CU by LDS). The BH kernel is held to one
-// by its LDS there and only loses schedule by the limit (6.03 -> 6.75 ms for 8,192 walkers).
-__global__ __launch_bounds__(64, 2) void k_vmc_energy(VmcDev v, EECoefV cf,
+// WAVES per SIMD (vmc_two_per_simd): left alone the compiler takes 274 registers and one wave
+// stays; at most 256 let two share a SIMD (20 atoms, 16,384 walkers: 2,725 -> 2,441 us, five
+// walkers per CU by LDS). The BH kernel is held to one by its LDS there and only loses schedule
+// by the limit (6.03 -> 6.75 ms for 8,192 walkers).
+template <int WAVES>
+__global__ __launch_bounds__(64, WAVES) void k_vmc_energy(VmcDev v, EECoefV cf,
                                                    const double* __restrict__ R, long n_w,
                                                    double* __restrict__ E,
                                                    double* __restrict__ dE) {
@@ -1554,8 +1558,12 @@ extern "C" xtc_status xtc_vmc_local_energy(const xtc_vmc_system* sys, const xtc_
   XTC_REQUIRE(lds <= VMC_LDS_MAX, "xtc_vmc_local_energy: basis too large for the walker's LDS");
   if (n_walkers == 0) return XTC_OK;
   size_t tk = timing_begin(TM_VMC_ENERGY, st);
-  hipLaunchKernelGGL(k_vmc_energy, dim3((unsigned)n_walkers), dim3(64), lds, st, v, cf, R,
-                     (long)n_walkers, E, dE);
+  auto go = [&](auto waves) {
+    hipLaunchKernelGGL(k_vmc_energy<waves.value>, dim3((unsigned)n_walkers), dim3(64), lds, st, v, cf,
+                       R, (long)n_walkers, E, dE);
+  };
+  if (vmc_two_per_simd((long)lds, (long)n_walkers)) go(std::integral_constant<int, 2>{});
+  else go(std::integral_constant<int, 1>{});
   XTC_CHECK_LAUNCH();
   timing_end(tk, st);
   return XTC_OK;
