@@ -70,11 +70,11 @@ inline unsigned cdiv(long a, long b) { return (unsigned)((a + b - 1) / b); }
 inline hipStream_t as_stream(void* s) { return (hipStream_t)s; }
 
 // ---------------------------------------------------------------------------
-// Generic FP64 GEMM (MFMA 16x16x4, tile 64x64x16):
+// Generic FP64 GEMM (MFMA 16x16x4; its tiles: gemm_f64.hip):
 //   C[m, n] = alpha * sn[n] * sum_k A[m, k] s[k] B[k, n]   (+ beta * D[m, n])
-// then an optional epilogue: C <- C * E[m, n] (Hadamard) or C <- C * C.
+// then an optional epilogue: C <- C * E[m, n] (Hadamard).
 // Strides are in elements; A/B may be k- or m/n-contiguous.
-enum Epilogue { EPI_NONE = 0, EPI_MUL_E = 1, EPI_SQUARE = 2 };
+enum Epilogue { EPI_NONE = 0, EPI_MUL_E = 1 };
 
 struct GemmArgs {
   long M, N, K;

@@ -168,11 +168,6 @@ __global__ void k_restore_shift(const double* __restrict__ src, double* __restri
   dst[t] = src[t] + ((i == k) ? shift : 0.0);
 }
 
-__global__ void k_square(double* __restrict__ x, long n) {
-  long t = (long)blockIdx.x * 256 + threadIdx.x;
-  if (t < n) x[t] = x[t] * x[t];
-}
-
 // sum of x[i stride]^2, in the order of i, 32 values requested at a time
 __device__ __forceinline__ double sum_squares(const double* x, long stride, int n) {
   constexpr int U = 32;

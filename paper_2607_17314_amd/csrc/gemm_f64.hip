@@ -219,7 +219,6 @@ __global__ __launch_bounds__(256, 2) void k_gemm_f64(GemmList list) {
           if (g.sn) v *= sn;
           if (g.beta != 0.0) v += g.beta * d[bj][r];
           if (g.epi == EPI_MUL_E) v *= e[bj][r];
-          else if (g.epi == EPI_SQUARE) v *= v;
           if (in(bj, r)) g.C[c0 + ((16 * bi + 4 * r) * g.c_sm + 16 * bj * g.c_sn)] = v;
         }
       }
