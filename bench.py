@@ -473,7 +473,7 @@ def exchange_bench(wl, grid, C_mo, chans, prec, log):
 def assembly_bench(wl, inter, width, log):
     """W = -K + dU for every p in panels of `width` orbitals into one reused panel buffer
     (FP64), after one prepare; then dh, f and E0. Per panel the product has
-    2 (width N_orb) N_orb^2 (4 N_mu) flops and writes width N_orb^3 FP64 elements."""
+    2 (width N_orb) N_orb^2 (2 N_mu) flops and writes width N_orb^3 FP64 elements."""
     import torch
 
     from paper_2607_17314_amd import _lib as L

@@ -523,7 +523,7 @@ xtc_status xtc_vmc_gn_step(int64_t n_walkers, int32_t n_params, const double* E,
  * per kernel launch), 9 exchange projections and pair products, 10 exchange X
  * products (operand splitting included), 11 the exchange's stage 1 on the projected
  * rows (split path), 12 the exchange's split X-product kernel alone (one entry per
- * launch), 13 the assembly panel kernel (one entry per launch), 14 VMC sampling,
+ * launch), 13 the assembly panels (one entry per panel and output), 14 VMC sampling,
  * 15 VMC local energies, 16 the Gauss-Newton step, 17 the pair-value generation of the BH
  * form in split precision (one entry per launch; its split products count under 8).
  * out: host [2 * XTC_TIMING_CATEGORIES]. Not thread-safe. */

@@ -117,10 +117,9 @@ __global__ __launch_bounds__(256, 2) void k_gemm_f64(GemmList list) {
       for (int j = 0; j < NI; ++j)
         acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(fa[s & 1][i], fb[s & 1][j], acc[i][j], 0, 0, 0);
   };
-  // Two k-tiles in flight beside the one being multiplied: during step 0 the next tile goes
-  // from registers to the other LDS buffer and the one after it is requested, so the loads
-  // have a whole tile's time to arrive and the stores are long done at the barrier before
-  // step 3.
+  // DEPTH k-tiles in registers beside the one being multiplied: during step 0 the next tile goes
+  // from registers to the other LDS buffer and the one DEPTH after it is requested, so the loads
+  // have DEPTH tiles' time to arrive and the stores are long done at the barrier before step 3.
   constexpr std::true_type whole{};
   constexpr std::false_type any{};
   int buf = 0;

@@ -48,8 +48,8 @@ namespace xtc {
 constexpr int PIV_BLOCK = 256;
 constexpr double RANK_TOL = 1e-14;
 constexpr int NCAND = 64;      // candidates per batch (one 64-row GEMM tile)
-constexpr int NPLAN = 48;      // steps planned per batch: two factor entries per VGPR pair in
-                               // the replay, and about twice the 20-30 steps a batch accepts
+constexpr int NPLAN = 48;      // steps planned per batch: a factor entry per VGPR pair in the
+                               // replay, and about twice the 20-30 steps a batch accepts
 constexpr int TOP_PTS = 512;   // points per block of the candidate search
 
 // The planned steps of a batch (k_plan) and what the replay found (k_replay).

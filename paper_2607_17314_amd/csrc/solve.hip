@@ -5,8 +5,9 @@
 //   T_1 = R_1 - acc_1,  Y_1 = inv(L_11) T_1  for the first of the two block rows
 //   acc_2 += L_21 Y_1,  T_2 = R_2 - acc_2,  Y_2 = inv(L_22) T_2  for the second.
 // Every wave owns 16 NI columns and all 128 rows, so that the last two lines stay in its
-// registers: the four registers of an MFMA result are the B operands of four MFMA steps. The products' operands go global -> registers ->
-// LDS in the pipeline of gemm_f64.hip, L shared by the four waves.
+// registers: the four registers of an MFMA result are the B operands of four MFMA steps. The
+// products' operands go global -> registers -> LDS in the pipeline of gemm_f64.hip, L shared by
+// the four waves.
 //
 // Bound: the FP64 matrix rate. As one product and one 64 x 64 product per block row, 48
 // launches, the results so far were read again for every 64 rows and the remainder went
@@ -43,7 +44,7 @@ __global__ __launch_bounds__(256, 2) void k_solve(const double* __restrict__ L,
   // acc = the K products of rows i0 .. i0 + 127 of L (L^T) from A and the columns from B
   auto products = [&](const double* A, const double* B, long rows, long K) {
     int tp = tid;
-    asm volatile("" : "+v"(tp));   // as above: no offsets kept from one step for the next
+    asm volatile("" : "+v"(tp));   // opaque: no offsets kept, as live registers, for the next step
     TileLoader<SM, !BACK, false, 1> la(A, BACK ? 1 : n, BACK ? n : 1, 0, rows, K, tp);
     TileLoader<BN, false, false, 1> lb(B, 1, ldo, n0, cn, K, tp);
     const int wa = la.store_at(tp), wb = lb.store_at(tp);
@@ -279,8 +280,9 @@ xtc_status solve_columns(const double* L, const double* linv, long n, long cn, c
   XTC_REQUIRE(n > 0 && n < (1L << 22), "fit solve: bad number of rows");   // 32-bit offsets
   if (cn <= 0) return XTC_OK;
   // Whole rounds of workgroups per CU, a round of 64-column ones taking 0.58 of the time of a
-  // round of 128-column ones (1,500 rows forward: 16,384 columns 0.82 ms against 1.30, 32,768
-  // 1.32 against 1.39, 40,000 2.09 against 2.33, 58,200 2.63 against 2.36).
+  // round of 128-column ones. A fit of xi alone, 128- and 64-column workgroups: 1,500 rows,
+  // 16,384 columns 4.31, 3.36 ms; 32,768: 4.74, 4.97; 40,000: 7.12, 6.59; 58,200: 7.68, 8.25;
+  // 3,000 rows, 32,768: 14.9, 15.7. Up to 300 rows the two are within 7% of each other.
   const double wide = 1.0 * cdiv(cdiv(cn, 128), 256), narrow = 0.58 * cdiv(cdiv(cn, 64), 256);
   auto go = [&](auto B, auto NI) {
     hipLaunchKernelGGL((k_solve<B.value, NI.value>), dim3(cdiv(cn, 64 * NI.value)), dim3(256), 0, st, L,

@@ -10,9 +10,9 @@
 // lane-parallel over shells and the occupied orbitals lane-parallel over (orbital,
 // AO slice), and keeps the inverses current with Sherman-Morrison updates. No state
 // crosses walkers, so one launch runs every sweep. The Gauss-Newton step is one
-// workgroup: its sums over the walkers are block reductions for a few parameters and
-// walker tiles staged in LDS for more, all in a fixed order, then a Cholesky solve in
-// LDS.
+// workgroup: its sums over the walkers are block reductions for a few parameters, column
+// sums and matrix products over walker tiles in LDS for more, all in a fixed order, then a
+// Cholesky solve in LDS.
 #include <cmath>
 #include <type_traits>
 #include "common.hpp"
